@@ -34,6 +34,7 @@ COMMON = [
 # places read-only MFMA operands (K/V or Q/dO fragments) in AGPRs.
 EXTRA = {
     "attn_f32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "gemm_bf16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "attn_fwd_bf16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "attn_bwd_bf16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
 }

@@ -244,17 +244,71 @@ __device__ __forceinline__ bf16x8 ld_tr(const uint16_t* X, int lo, int hi) {
   return as_bf16x8(u32x4{a2.x, a2.y, b2.x, b2.y});
 }
 
-// GELU in its tanh form, x/2 (1 + tanh(sqrt(2/pi) (x + 0.044715 x^3))), and
-// its derivative; shared by the GEMM epilogues and the recompute kernel so
-// the forward and the backward evaluate the same expression.
-__device__ __forceinline__ float gelu_tanh(float x) {
-  const float u = 0.7978845608028654f * (x + 0.044715f * x * x * x);
-  return 0.5f * x * (1.f + tanhf(u));
+// ------------------------------------------- 16x16x32 MFMA tiles
+// v_mfma_f32_16x16x32_bf16: lane l (i = l % 16, g = l / 16) holds row / column
+// i and 8 k-values of A / B, and of C column i, rows 4 g + v, v = 0..3.  At
+// the power limit it is the cheaper form of the same product: 256 CUs of
+// nothing but MFMAs on N(0,1) operands hold 2.03-2.06 PFLOP/s with it and
+// 1.72-1.81 with 32x32x16.
+__device__ __forceinline__ f32x4 mfma16(const bf16x8& a, const bf16x8& b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
+
+// LDS tile [rows][D] for it: as XTile, with the swizzle f chosen for its
+// access patterns:
+//   * natural reads of 16 consecutive rows, one chunk each; for D = 64 also of
+//     rows 8 (i / 4) + 4 j + i % 4 (nat_perm);
+//   * transposed reads of 8 consecutive rows x 2 chunks per 32 lanes.
+template <int D>
+struct YTile {
+  static constexpr int P = D;
+  static constexpr int CG = D / 8;
+  static constexpr int RPI = 512 / D;
+  static __device__ __forceinline__ int f(int r) {
+    if constexpr (D == 128) {
+      return ((r & 7) << 1) | ((r >> 3) & 1);
+    } else {
+      return ((r >> 3) & 1) | (((r >> 1) & 1) << 1) | ((((r >> 2) ^ (r >> 4)) & 1) << 2);
+    }
+  }
+  // Natural operand, k-step kk (32 wide) of the rows rb + l % 16 (rb % 32 == 0
+  // or 16): element offset with the row base included.
+  static __device__ __forceinline__ int nat(int lane, int kk, int rb) {
+    const int r = rb + (lane & 15), g = lane >> 4;
+    return r * P + 8 * ((4 * kk + g) ^ f(r));
+  }
+  // The same for rows rb + 8 (i / 4) + 4 j + i % 4: tiles j = 0, 1 then give
+  // each lane of C eight consecutive rows 8 g.. of the 32.
+  static __device__ __forceinline__ int nat_perm(int lane, int kk, int rb, int j) {
+    const int i = lane & 15, g = lane >> 4, r = rb + 8 * (i >> 2) + 4 * j + (i & 3);
+    return r * P + 8 * ((4 * kk + g) ^ f(r));
+  }
+  // Transposed operand: lane l gets column 16 blk + i of rows 4 g + 0..3 (add
+  // 16 P for rows 16.. and so on; the swizzle repeats every 16 rows).
+  static __device__ __forceinline__ int tr(int lane, int blk) {
+    const int g = lane >> 4, e = (lane >> 2) & 3, a = lane & 3, r = 4 * g + e;
+    return r * P + 8 * ((2 * blk + (a >> 1)) ^ f(r)) + 4 * (a & 1);
+  }
+  static __device__ __forceinline__ int dma(int lane, int u, int64_t row_stride) {
+    const int row = RPI * u + lane / CG, p = lane % CG;
+    return (int)((row * row_stride + 8 * (p ^ f(row))) * (int64_t)sizeof(uint16_t));
+  }
+};
+
+// GELU in its tanh form, x/2 (1 + tanh(u)), u = sqrt(2/pi) (x + 0.044715 x^3),
+// and its derivative; shared by the GEMM epilogues and the recompute kernel
+// so the forward and the backward evaluate the same expression.  Written with
+// the logistic function, (1 + tanh(u)) / 2 = 1 / (1 + exp(-2u)): one exp2 and
+// one reciprocal (each within 1 ulp) in place of tanhf's branches, and no
+// cancellation in 1 + tanh(u) for negative u.
+__device__ __forceinline__ float gelu_gate(float x) {
+  const float u2 = (-2.f * 0.7978845608028654f * kLog2e) * (x + 0.044715f * x * x * x);
+  return __builtin_amdgcn_rcpf(1.f + fast_exp2(u2));
+}
+__device__ __forceinline__ float gelu_tanh(float x) { return x * gelu_gate(x); }
 __device__ __forceinline__ float gelu_tanh_grad(float x) {
-  const float u = 0.7978845608028654f * (x + 0.044715f * x * x * x);
-  const float t = tanhf(u);
-  return 0.5f * (1.f + t) + 0.5f * x * (1.f - t * t) * 0.7978845608028654f * (1.f + 3.f * 0.044715f * x * x);
+  const float s = gelu_gate(x);
+  return s + 2.f * x * s * (1.f - s) * 0.7978845608028654f * (1.f + 3.f * 0.044715f * x * x);
 }
 
 }  // namespace sppo

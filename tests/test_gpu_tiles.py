@@ -7,6 +7,8 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import transformer_layer as T
+from paper_2503_10377_amd import sppo as L
 from paper_2503_10377_amd.chunked import ChunkedAttention
 from paper_2503_10377_amd.inputs import make_inputs
 from parity import check_all, to_np
@@ -62,3 +64,52 @@ def test_fp32_nonfinite_rows_stay_behind_the_mask(D):
     assert not np.isfinite(got["dv"][:, 0]).all()
     for n in ("dk", "dv"):
         np.testing.assert_allclose(got[n][:, 1:], ref[n][:, 1:], rtol=0, atol=2e-6, err_msg=n)
+
+
+def gemm(lay, M, N, K, a, b, epi="bf16", aux=None, c=None):
+    lda, ldb = a.shape[1], b.shape[1]
+    if c is None:
+        c = torch.full((M, N), 7.0, device="cuda", dtype=torch.float32 if "f32" in epi else torch.bfloat16)
+    L.sppo_gemm_bf16(lay, M, N, K, a, lda, b, ldb, c, N, epi, aux, N if aux is not None else 0)
+    torch.cuda.synchronize()
+    return c
+
+
+# 64, 128 and 256 tiles (the last from 4097 x 4100 on), one k-block, an odd and an even number of them.
+@pytest.mark.parametrize("M,N,K", [(63, 68, 64), (65, 60, 192), (64, 1028, 640), (129, 2052, 128), (127, 4100, 64),
+                                   (4097, 4100, 64), (4095, 4092, 192)])
+def test_gemm_nt_tiles(M, N, K):
+    """Every epilogue of NT against the fp64 product; the rows that a product
+    of the first 60 rows (another tile) computes have the same bits."""
+    announce(f"gemm nt tiles {M}x{N}x{K}")
+    g = torch.Generator().manual_seed(M + N + K)
+    a, b, x = (torch.randn(*s, generator=g).to(torch.bfloat16) for s in ((M, K), (N, K), (M, N)))
+    ad, bd, xd = a.cuda(), b.cuda(), x.cuda()
+    ref = to_np(a) @ to_np(b).T
+    xr = to_np(x)
+    for epi, want in (("bf16", ref), ("add_bf16", ref + xr), ("dgelu", ref * T.gelu_grad(xr)), ("gelu", None),
+                      ("f32", ref), ("acc_f32", ref + 7.0)):
+        aux = xd.clone() if epi in ("add_bf16", "dgelu", "gelu") else None
+        got = gemm("nt", M, N, K, ad, bd, epi, aux)
+        sub = gemm("nt", min(M, 60), N, K, ad[:60], bd, epi, None if aux is None else xd[:60].clone())
+        assert torch.equal(got[:60], sub), epi
+        if epi == "gelu":
+            pre = to_np(aux)
+            assert np.abs(pre - ref).max() <= 8e-3 * np.abs(ref).max()
+            want = T.gelu(pre)
+        tol = 1e-5 if "f32" in epi else 8e-3
+        assert np.abs(to_np(got) - want).max() <= tol * np.abs(want).max() + 1e-6, epi
+
+
+@pytest.mark.parametrize("M,N,K", [(256, 256, 64), (512, 768, 129), (1024, 4096, 63), (4096, 4352, 150)])
+def test_gemm_tn_tiles(M, N, K):
+    announce(f"gemm tn tiles {M}x{N}x{K}")
+    g = torch.Generator().manual_seed(M + N + K)
+    a, b = (torch.randn(K, n, generator=g).to(torch.bfloat16) for n in (M, N))
+    ref = to_np(a).T @ to_np(b)
+    got = gemm("tn", M, N, K, a.cuda(), b.cuda(), "f32")
+    assert np.abs(to_np(got) - ref).max() <= 1e-5 * np.abs(ref).max() + 1e-6
+    got = gemm("tn", M, N, K, a.cuda(), b.cuda(), "acc_f32", c=got)
+    assert np.abs(to_np(got) - 2 * ref).max() <= 1e-5 * np.abs(2 * ref).max() + 1e-6
+    got = gemm("tn", M, N, K, a.cuda(), b.cuda(), "bf16")
+    assert np.abs(to_np(got) - ref).max() <= 8e-3 * np.abs(ref).max()
