@@ -37,8 +37,6 @@
 #include "sppo_kernels.h"
 #include "tile_common.h"
 
-#include <atomic>
-
 namespace sppo {
 namespace {
 
@@ -425,18 +423,6 @@ __global__ __launch_bounds__(BT == 128 ? 512 : 256, 1) void gemm_small_kernel(Ge
   if (kb < nkb) step(IC<0>{});
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));  // no LDS-DMA in flight past the end
   store_tile<TN, EPI, MI>(g, m0 + 16 * MI * wm, n0 + 32 * wn, acc);
-}
-
-// Compute units of the current device (asked of the runtime once per device).
-int device_cus() {
-  constexpr int kMaxDevices = 64;
-  static std::atomic<int> known[kMaxDevices];
-  int dev = -1, n = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 256;
-  if ((n = known[dev].load(std::memory_order_relaxed)) > 0) return n;
-  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1) return 256;
-  known[dev].store(n, std::memory_order_relaxed);
-  return n;
 }
 
 template <int TN, int EPI>

@@ -13,6 +13,10 @@ namespace sppo {
 // the last context-free call (or of sppo_create).
 void set_thread_error(const std::string& msg);
 
+// Compute units of the current device (asked of the runtime once per device;
+// 256 if it does not say).
+int device_cus();
+
 // Arguments of one chunk's attention kernels.  Chunk-local tensors (q, o,
 // dout, dq, lse) hold rows [c0, c1) only; k/v/dk/dv are full-length.
 struct ChunkArgs {

@@ -55,6 +55,12 @@ __device__ __forceinline__ bf16x8 pack_bf16x8(float x0, float x1, float x2, floa
   return r;
 }
 
+__device__ __forceinline__ uint32_t pack_bf16x2(float x0, float x1) {
+  bf16x2 r;
+  r.x = (__bf16)x0; r.y = (__bf16)x1;
+  return __builtin_bit_cast(uint32_t, r);
+}
+
 // Four fp32 values rounded to bf16 as two packed dwords.
 __device__ __forceinline__ u32x2 pack_bf16x4(float x0, float x1, float x2, float x3) {
   bf16x2 lo, hi;
@@ -84,6 +90,16 @@ __device__ __forceinline__ float max_xor32(float x) {
 __device__ __forceinline__ float sum_xor32(float x) {
   auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// The same over the four 16-lane groups (xor 16, then xor 32).
+__device__ __forceinline__ float max_groups(float x) {
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return max_xor32(max_nc(__uint_as_float(r[0]), __uint_as_float(r[1])));
+}
+__device__ __forceinline__ float sum_groups(float x) {
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return sum_xor32(__uint_as_float(r[0]) + __uint_as_float(r[1]));
 }
 
 // ------------------------------------------------------ buffer resources
@@ -256,9 +272,13 @@ __device__ __forceinline__ f32x4 mfma16(const bf16x8& a, const bf16x8& b, const 
 
 // LDS tile [rows][D] for it: as XTile, with the swizzle f chosen for its
 // access patterns:
-//   * natural reads of 16 consecutive rows, one chunk each; for D = 64 also of
-//     rows 8 (i / 4) + 4 j + i % 4 (nat_perm);
-//   * transposed reads of 8 consecutive rows x 2 chunks per 32 lanes.
+//   * natural reads: 16 consecutive rows, chunk 4 kk + g; for D = 64 also of
+//     rows 8 (i / 4) + 4 j + i % 4 (nat_perm).  A ds_read_b128 serves lanes
+//     {0-3, 12-15, 20-27} together, then {4-11, 16-19, 28-31} (and 32 on), so
+//     half of a group's rows come with the neighbouring chunk: f flips chunk
+//     bit 0 with row bit 2 (with row bit 3 instead, every natural read took
+//     twice its cycles);
+//   * transposed reads: 8 consecutive rows x 2 chunks per 32 lanes.
 template <int D>
 struct YTile {
   static constexpr int P = D;
@@ -266,9 +286,9 @@ struct YTile {
   static constexpr int RPI = 512 / D;
   static __device__ __forceinline__ int f(int r) {
     if constexpr (D == 128) {
-      return ((r & 7) << 1) | ((r >> 3) & 1);
+      return ((r & 7) << 1) | ((r >> 2) & 1);
     } else {
-      return ((r >> 3) & 1) | (((r >> 1) & 1) << 1) | ((((r >> 2) ^ (r >> 4)) & 1) << 2);
+      return ((r >> 2) & 1) | (((r >> 1) & 1) << 1) | ((((r >> 2) ^ (r >> 4)) & 1) << 2);
     }
   }
   // Natural operand, k-step kk (32 wide) of the rows rb + l % 16 (rb % 32 == 0
@@ -284,7 +304,8 @@ struct YTile {
     return r * P + 8 * ((4 * kk + g) ^ f(r));
   }
   // Transposed operand: lane l gets column 16 blk + i of rows 4 g + 0..3 (add
-  // 16 P for rows 16.. and so on; the swizzle repeats every 16 rows).
+  // 16 P for rows 16.. and so on: for D = 128 the swizzle repeats every 8 rows,
+  // for D = 64 row bit 4 swaps column blocks blk and blk ^ 2).
   static __device__ __forceinline__ int tr(int lane, int blk) {
     const int g = lane >> 4, e = (lane >> 2) & 3, a = lane & 3, r = 4 * g + e;
     return r * P + 8 * ((2 * blk + (a >> 1)) ^ f(r)) + 4 * (a & 1);

@@ -113,3 +113,25 @@ def test_gemm_tn_tiles(M, N, K):
     assert np.abs(to_np(got) - 2 * ref).max() <= 1e-5 * np.abs(2 * ref).max() + 1e-6
     got = gemm("tn", M, N, K, a.cuda(), b.cuda(), "bf16")
     assert np.abs(to_np(got) - ref).max() <= 8e-3 * np.abs(ref).max()
+
+
+# The split attention kernels (64 query rows, 32 or 64 keys a workgroup, four or two parts) and the wide ones beside
+# them: one row, one below, at and above a sub-block (32), a workgroup (64) and a wide tile (128), chunk boundaries off
+# all of them, GQA; the last two have enough heads for the wide kernels in some launches and the split ones in others.
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("B,Hq,Hkv,offsets", [(1, 2, 1, [0, 1, 2]), (2, 2, 2, [0, 31, 63, 96]), (1, 6, 2, [0, 33, 130, 300]),
+                                              (1, 4, 1, [0, 64, 192, 449]), (1, 3, 3, [0, 127, 255, 700]),
+                                              (2, 32, 8, [0, 257, 600]), (1, 64, 16, [0, 300, 333, 1100])])
+def test_bf16_split_and_wide(D, B, Hq, Hkv, offsets):
+    gpu, ref, off = run_case(B, offsets[-1], Hq, Hkv, D, "bf16", offsets=offsets, seed=19)
+    check_all(gpu, ref, "bf16", off)
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,offsets", [(8, 2, 128, [0, 500, 1000, 1777]), (16, 16, 64, [0, 700, 1500])])
+def test_bf16_evicting_walk_equals_resident_by_kernel_choice(Hq, Hkv, D, offsets):
+    """The evicting walk's last backward runs its dK/dV once per KV chunk: each
+    launch covers fewer keys but takes the same kernel, so the bits agree."""
+    res = [run_case(1, offsets[-1], Hq, Hkv, D, "bf16", offsets=offsets, seed=23, offload=o)[0]
+           for o in ("qkvol", "qkvol_evict")]
+    for n in ("o", "lse", "dq", "dk", "dv"):
+        assert np.array_equal(res[0][n], res[1][n]), n
