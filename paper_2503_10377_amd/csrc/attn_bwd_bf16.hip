@@ -11,7 +11,7 @@
 //             query rows of every head of the GQA group stream through LDS in
 //             32-row sub-blocks, and per sub-block
 //               S = Q K^T, dP = dO V^T, P = exp2(S C - LSE2), dS = P (dP - Delta)
-//               dV += P^T dO,  dK += dS^T Q
+//               dV^T += dO^T P,  dK^T += Q^T dS
 //             The kernel is persistent (as many workgroups as the CUs
 //             hold at once, one per CU at its register use): each XCD
 //             takes key tiles from its own queue, in the XCD-grouped order,
@@ -26,7 +26,17 @@
 // n's P and dS, then the gradient MFMAs of sub-block n run.  The order of
 // every step is fixed with sched_barrier, so operand reads sit a few MFMAs
 // ahead of their use.  Sub-blocks that need the causal mask are done one at
-// a time, outside the pipeline.
+// a time, outside the pipeline.  Grids too small for the chip take the split
+// kernels further down.
+//
+// Every product is the 16x16x32 MFMA: per step as many cycles of the matrix
+// pipe as with 32x32x16, for less energy, and the LSE2 / Delta records take
+// half the LDS reads.  At the power limit the clock rose (dK/dV 1.89 -> 2.11
+// GHz, dQ 1.81 -> 2.11 at 32K tokens x 32 heads) while the lone wave on each
+// SIMD, which now issues twice the MFMAs, keeps the matrix pipe less busy (0.60
+// -> 0.53, 0.64 -> 0.56): dK/dV -1.2%, dQ -3.1% at 128K, both -5% at D = 64.
+// What is left is the one wave's instruction stream: moving half the
+// exponentials from the S/dP phase to the gradient phase changed nothing.
 #include "sppo_kernels.h"
 #include "tile_common.h"
 
@@ -38,20 +48,15 @@ constexpr int kDqRows = 128;  // query rows per dQ workgroup (4 waves x 32)
 constexpr int kSB = 32;       // rows (dK/dV) or keys (dQ) per sub-block
 constexpr int kRing = 6;      // LDS ring slots
 constexpr int kAhead = 5;     // sub-blocks loaded ahead of the one in use
-// LSE2 groups loaded ahead of their use in the softmax (0: right before;
-// 1: 1.3% faster at 128K, measured when the Delta groups went with them;
-// all four at the step start: 0.9%).
-constexpr int kLdAhead = 1;
-// The B phase's first three transposed reads are issued in the last MFMA
-// slots of the A phase, which read nothing else (dQ 1% faster than issuing
-// them right before B).
-constexpr bool kEarlyTr = true;
 // Each step's barrier also waits for sub-block n+2, so the B phase of step n
 // can read A(n+1)'s first natural operands in its last MFMA slots (which read
-// nothing else): dK/dV 0.6% faster than reading them right after the barrier.
-constexpr bool kEarlyA = true;
-constexpr bool kEarlyAq = true;  // the same for the dQ kernel: 2.1% faster
+// nothing else), and A's last slots read B's first transposed operands.
 static_assert(kAhead == kRing - 1, "a slot is refilled right after its last reader");
+
+// S or dP of a 32 x 32 sub-block: 16 x 16 tiles, [row tile][column tile].
+struct S4 {
+  f32x4 x[2][2];
+};
 
 // ------------------------------------------------------------------ Delta
 template <int D>
@@ -89,8 +94,8 @@ __global__ __launch_bounds__(256) void bwd_pre_bf16_kernel(ChunkArgs a) {
 // ------------------------------------------------------------------ dK dV
 template <int D>
 __global__ __launch_bounds__(256, 1) void bwd_dkdv_bf16_kernel(ChunkArgs a) {
-  using T = XTile<D>;
-  constexpr int P = T::P, NK = D / 16, ND = D / 32;
+  using T = Tile<D>;
+  constexpr int P = T::P, NK = D / 32, ND = D / 16;  // k-steps of S and dP, d tiles
   constexpr int IPWQ = (kSB / T::RPI) / 4;  // DMA instructions per wave per tensor per sub-block
   static_assert(IPWQ >= 1 && IPWQ * 4 * T::RPI == kSB, "sub-block splits over 4 waves");
   constexpr int DMA_PER_SB = 2 * IPWQ + 1;  // Q, dO, and one for the [LSE2 | -Delta] record
@@ -110,7 +115,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dkdv_bf16_kernel(ChunkArgs a) {
   auto lbuf = [&](auto I) -> float* { return REC[decltype(I)::value]; };
 
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l32 = lane & 31, g = lane >> 5;
+  const int l16 = lane & 15, g = lane >> 4;
   // Key tiles in the XCD-grouped order (the tiles of a KV head one after
   // another): XCD x owns positions [x T / 8, (x+1) T / 8) of the T tiles.
   // Thread 0 takes the next position from this XCD's queue, or when that
@@ -144,7 +149,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dkdv_bf16_kernel(ChunkArgs a) {
   const int64_t c0 = a.c0, c1 = a.c1, s = c1 - c0;
   const int64_t kv1 = a.kv1;
   const int64_t k0 = a.kv0 + (int64_t)gp.x * kKvKeys;
-  const int64_t j = k0 + 32 * w + l32;  // this lane's key
+  const int64_t j = k0 + 32 * w + l16;  // this lane's keys: j and j + 16
   const float C = a.scale * kLog2e;
 
   // Query sub-blocks (chunk-local, 32 rows from c0): [sb_begin, sb_u) need
@@ -158,13 +163,10 @@ __global__ __launch_bounds__(256, 1) void bwd_dkdv_bf16_kernel(ChunkArgs a) {
 
   int nat[NK];
 #pragma unroll
-  for (int kk = 0; kk < NK; ++kk) nat[kk] = T::nat(lane, kk);
-  int tro[ND][2];
+  for (int kk = 0; kk < NK; ++kk) nat[kk] = T::nat(lane, kk, 0);
+  int tro[ND];
 #pragma unroll
-  for (int db = 0; db < ND; ++db) {
-    tro[db][0] = T::tr(lane, db, 0);
-    tro[db][1] = T::tr(lane, db, 1);
-  }
+  for (int dt = 0; dt < ND; ++dt) tro[dt] = T::tr(lane, dt);
   const int64_t qstride = (int64_t)a.Hq * D;
   int dmaq[IPWQ];
 #pragma unroll
@@ -175,20 +177,22 @@ __global__ __launch_bounds__(256, 1) void bwd_dkdv_bf16_kernel(ChunkArgs a) {
   const float* lsrc = (w < 2) ? a.lse2 : a.delta;
   const int ldst = 32 * (w >> 1) + 16 * (w & 1);
 
-  bf16x8 kf[NK], vf[NK];
-  {
-    const int64_t off = ((b * a.S + j) * a.Hkv + hk) * D;
+  bf16x8 kf[2][NK], vf[2][NK];
+#pragma unroll
+  for (int kt = 0; kt < 2; ++kt) {
+    const int64_t jk = j + 16 * kt;
+    const int64_t off = ((b * a.S + jk) * a.Hkv + hk) * D;
     const uint16_t* krow = static_cast<const uint16_t*>(a.k) + off;
     const uint16_t* vrow = static_cast<const uint16_t*>(a.v) + off;
 #pragma unroll
     for (int kk = 0; kk < NK; ++kk) {
-      kf[kk] = j < kv1 ? as_bf16x8(ld_global16(krow + 16 * kk + 8 * g)) : bf16x8{};
-      vf[kk] = j < kv1 ? as_bf16x8(ld_global16(vrow + 16 * kk + 8 * g)) : bf16x8{};
+      kf[kt][kk] = jk < kv1 ? as_bf16x8(ld_global16(krow + 32 * kk + 8 * g)) : bf16x8{};
+      vf[kt][kk] = jk < kv1 ? as_bf16x8(ld_global16(vrow + 32 * kk + 8 * g)) : bf16x8{};
     }
   }
-  f32x16 dk[ND], dv[ND];
+  f32x4 dk[ND][2], dv[ND][2];  // dK^T, dV^T: [d tile][key tile]
 #pragma unroll
-  for (int db = 0; db < ND; ++db) dk[db] = dv[db] = f32x16{};
+  for (int dt = 0; dt < ND; ++dt) dk[dt][0] = dk[dt][1] = dv[dt][0] = dv[dt][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // DMA of query sub-block sb of head h into a slot; rows past the chunk load
   // zeros, so every call issues DMA_PER_SB instructions per wave.
@@ -243,42 +247,38 @@ __global__ __launch_bounds__(256, 1) void bwd_dkdv_bf16_kernel(ChunkArgs a) {
     la += kSB * 4;
     rem -= kSB;
   };
-  auto tr_rd = [&](const uint16_t* X, int hh, int db) {
-    return ld_tr(X, tro[db][0] + 16 * hh * P, tro[db][1] + 16 * hh * P);
-  };
-  // -Delta of the 16 rows 8 (v/4) + 4 g + v%4 of a sub-block, from its record:
-  // the initial value of its dP accumulator.
-  auto ndelta = [&](const float* ld) {
-    f32x16 x;
+  // Natural operand of the 16 rows 16 t.. of a sub-block, k-step kk, and
+  // transposed operand of its 32 rows, d tile dt (D = 64: rows 16.. swap the
+  // two k-steps' chunks and column blocks dt, dt ^ 2).
+  auto nat_rd = [&](const uint16_t* X, int t, int kk) { return ld_nat(X + 16 * t * P, nat[D == 64 ? kk ^ t : kk]); };
+  auto tr_rd = [&](const uint16_t* X, int dt) { return ld_tr(X, tro[dt], tro[D == 64 ? dt ^ 2 : dt] + 16 * P); };
+  // LSE2 and -Delta (the initial value of the dP accumulators) of this lane's
+  // rows 16 qt + 4 g + 0..3 of a sub-block, from its record.
+  auto rec_rd = [&](const float* ld, int qt) { return *reinterpret_cast<const f32x4*>(ld + 16 * qt + 4 * g); };
+  // S = Q K^T and dP - Delta = dO V^T - Delta of one sub-block (lane <-> key).
+  auto sdp = [&](const uint16_t* Qs, const uint16_t* Os, const f32x4 (&nd)[2], S4& sv, S4& dp) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const float4 t = *reinterpret_cast<const float4*>(ld + 32 + 8 * k + 4 * g);
-      x[4 * k] = t.x;
-      x[4 * k + 1] = t.y;
-      x[4 * k + 2] = t.z;
-      x[4 * k + 3] = t.w;
-    }
-    return x;
-  };
-  // S = Q K^T and dP - Delta = dO V^T - Delta of one sub-block (lane <-> key);
-  // dp holds -Delta on entry.
-  auto sdp = [&](const uint16_t* Qs, const uint16_t* Os, f32x16& sv, f32x16& dp) {
-    sv = mfma32(ld_nat(Qs, nat[0]), kf[0], f32x16{});
-    dp = mfma32(ld_nat(Os, nat[0]), vf[0], dp);
+    for (int kk = 0; kk < NK; ++kk) {
 #pragma unroll
-    for (int kk = 1; kk < NK; ++kk) {
-      sv = mfma32(ld_nat(Qs, nat[kk]), kf[kk], sv);
-      dp = mfma32(ld_nat(Os, nat[kk]), vf[kk], dp);
+      for (int qt = 0; qt < 2; ++qt) {
+        const bf16x8 qx = nat_rd(Qs, qt, kk), ox = nat_rd(Os, qt, kk);
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt) {
+          sv.x[qt][kt] = mfma16(qx, kf[kt][kk], kk == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : sv.x[qt][kt]);
+          dp.x[qt][kt] = mfma16(ox, vf[kt][kk], kk == 0 ? nd[qt] : dp.x[qt][kt]);
+        }
+      }
     }
   };
-  // dV += P^T dO, dK += dS^T Q of one sub-block.
+  // dV^T += dO^T P, dK^T += Q^T dS of one sub-block.
   auto grads = [&](const uint16_t* Qs, const uint16_t* Os, const bf16x8 (&pb)[2], const bf16x8 (&dsb)[2]) {
 #pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
+    for (int dt = 0; dt < ND; ++dt) {
+      const bf16x8 ox = tr_rd(Os, dt), qx = tr_rd(Qs, dt);
 #pragma unroll
-      for (int db = 0; db < ND; ++db) {
-        dv[db] = mfma32(pb[hh], tr_rd(Os, hh, db), dv[db]);
-        dk[db] = mfma32(dsb[hh], tr_rd(Qs, hh, db), dk[db]);
+      for (int kt = 0; kt < 2; ++kt) {
+        dv[dt][kt] = mfma16(ox, pb[kt], dv[dt][kt]);
+        dk[dt][kt] = mfma16(qx, dsb[kt], dk[dt][kt]);
       }
     }
   };
@@ -296,23 +296,25 @@ __global__ __launch_bounds__(256, 1) void bwd_dkdv_bf16_kernel(ChunkArgs a) {
       __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
       __syncthreads();
       const float* ld = lbuf(IC<0>{});
-      f32x16 sv, dp = ndelta(ld);
-      sdp(qbuf(IC<0>{}), obuf(IC<0>{}), sv, dp);
+      const f32x4 nd[2] = {rec_rd(ld + 32, 0), rec_rd(ld + 32, 1)}, lg[2] = {rec_rd(ld, 0), rec_rd(ld, 1)};
+      S4 sv, dp;
+      sdp(qbuf(IC<0>{}), obuf(IC<0>{}), nd, sv, dp);
       const int64_t r0g = c0 + (int64_t)sb * kSB;  // global row of the sub-block's first row
-      float p[16], ds[16];
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int qi = 8 * (v / 4) + 4 * g + (v % 4);
-        float pv = fast_exp2(sv[v] * C - ld[qi]);
-        if (j > r0g + qi) pv = 0.f;  // key j sees row r iff j <= r
-        p[v] = pv;
-        ds[v] = pv * dp[v];
-      }
       bf16x8 pb[2], dsb[2];
-      pb[0] = pack_bf16x8(p[0], p[1], p[2], p[3], p[4], p[5], p[6], p[7]);
-      pb[1] = pack_bf16x8(p[8], p[9], p[10], p[11], p[12], p[13], p[14], p[15]);
-      dsb[0] = pack_bf16x8(ds[0], ds[1], ds[2], ds[3], ds[4], ds[5], ds[6], ds[7]);
-      dsb[1] = pack_bf16x8(ds[8], ds[9], ds[10], ds[11], ds[12], ds[13], ds[14], ds[15]);
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt) {
+        float p[8], ds[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int qt = e >> 2, v = e & 3;
+          float pv = fast_exp2(sv.x[qt][kt][v] * C - lg[qt][v]);
+          if (j + 16 * kt > r0g + 16 * qt + 4 * g + v) pv = 0.f;  // key j sees row r iff j <= r
+          p[e] = pv;
+          ds[e] = pv * dp.x[qt][kt][v];
+        }
+        pb[kt] = pack_bf16x8(p[0], p[1], p[2], p[3], p[4], p[5], p[6], p[7]);
+        dsb[kt] = pack_bf16x8(ds[0], ds[1], ds[2], ds[3], ds[4], ds[5], ds[6], ds[7]);
+      }
       grads(qbuf(IC<0>{}), obuf(IC<0>{}), pb, dsb);
     }
 
@@ -325,118 +327,127 @@ __global__ __launch_bounds__(256, 1) void bwd_dkdv_bf16_kernel(ChunkArgs a) {
     stream_issue(qbuf(IC<2>{}), obuf(IC<2>{}), lbuf(IC<2>{}));
     stream_issue(qbuf(IC<3>{}), obuf(IC<3>{}), lbuf(IC<3>{}));
     stream_issue(qbuf(IC<4>{}), obuf(IC<4>{}), lbuf(IC<4>{}));
-    // With kEarlyA, sub-blocks 0 and 1 land before the loop and step 0's
-    // first natural operands are read here; later steps get theirs from the
-    // end of the previous B phase.
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm((kAhead - (kEarlyA ? 2 : 1)) * DMA_PER_SB));
+    // Sub-blocks 0 and 1 land before the loop and step 0's first natural
+    // operands are read here; later steps get theirs from the end of the
+    // previous B phase.
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm((kAhead - 2) * DMA_PER_SB));
     __syncthreads();
-    f32x16 sa, da = ndelta(lbuf(IC<0>{})), sb2, db2;
-    sdp(qbuf(IC<0>{}), obuf(IC<0>{}), sa, da);
+    S4 sa, da, sb2, db2;
+    f32x4 nd[2] = {rec_rd(lbuf(IC<0>{}) + 32, 0), rec_rd(lbuf(IC<0>{}) + 32, 1)};
+    sdp(qbuf(IC<0>{}), obuf(IC<0>{}), nd, sa, da);
+    // Natural operand o of a sub-block's A phase: k-step o / 4, row tile
+    // (o / 2) % 2, Q (o even) or dO (o odd).
+    auto nat_of = [&](const uint16_t* Qx, const uint16_t* Ox, int o) {
+      return nat_rd((o & 1) ? Ox : Qx, (o >> 1) & 1, o >> 2);
+    };
     bf16x8 opn[4];
-    if (kEarlyA) {
+    f32x4 lg[2] = {rec_rd(lbuf(IC<0>{}), 0), rec_rd(lbuf(IC<0>{}), 1)};
 #pragma unroll
-      for (int m = 0; m < 4; ++m) opn[m] = ld_nat((m & 1) ? obuf(IC<1>{}) : qbuf(IC<1>{}), nat[m >> 1]);
-      db2 = ndelta(lbuf(IC<1>{}));
-    }
-    // Step n in slot I: A(n) reads slot I+1 (natural) and slot I's record;
-    // B(n) reads slot I (transposed) and, in its last MFMA slots, A(n+1)'s
-    // first natural operands from slot I+2.  At its start sub-blocks n+1 and
-    // n+2 have landed (only n+3, n+4 may still be loading); then sub-block
-    // n+5 goes to slot I+5 = I-1, free since step n-1.  dnext holds -Delta of
-    // sub-block n+1 on entry (read in B(n-1)); B(n) leaves -Delta of n+2 in
-    // dcur, which is step n+1's dnext.
-    auto step = [&](int n, auto sl, f32x16& scur, f32x16& dcur, f32x16& snext, f32x16& dnext) {
+    for (int o = 0; o < 4; ++o) opn[o] = nat_of(qbuf(IC<1>{}), obuf(IC<1>{}), o);
+    nd[0] = rec_rd(lbuf(IC<1>{}) + 32, 0);
+    nd[1] = rec_rd(lbuf(IC<1>{}) + 32, 1);
+    // Step n in slot I: A(n) reads slot I+1 (natural); B(n) reads slot I
+    // (transposed) and, in its last slots, A(n+1)'s first natural operands and
+    // -Delta from slot I+2 and LSE2 of sub-block n+1.  At its start sub-blocks
+    // n+1 and n+2 have landed (only n+3, n+4 may still be loading); then
+    // sub-block n+5 goes to slot I+5 = I-1, free since step n-1.  nd holds
+    // -Delta of sub-block n+1 and lg LSE2 of sub-block n on entry.
+    auto step = [&](auto sl, S4& scur, S4& dcur, S4& snext, S4& dnext) {
       constexpr int I = decltype(sl)::value;
       constexpr int I1 = (I + 1) % kRing, I2 = (I + 2) % kRing, I5 = (I + kAhead) % kRing;
-      __builtin_amdgcn_s_waitcnt(waitcnt_vm((kAhead - (kEarlyA ? 3 : 2)) * DMA_PER_SB));
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm((kAhead - 3) * DMA_PER_SB));
       __syncthreads();
       stream_issue(qbuf(IC<I5>{}), obuf(IC<I5>{}), lbuf(IC<I5>{}));
       const uint16_t* Qn = qbuf(IC<I1>{});
       const uint16_t* On = obuf(IC<I1>{});
       const uint16_t* Qc = qbuf(IC<I>{});
       const uint16_t* Oc = obuf(IC<I>{});
-      const float* ld = lbuf(IC<I>{});
-      if (!kEarlyA) dnext = ndelta(lbuf(IC<I1>{}));
-      // A(n): MFMA m (NA of them) is S(n+1) (m even) or dP(n+1) (m odd),
-      // k-step m/2; its operand is read four MFMAs ahead.  The VALU turns the
-      // 16 elements of S(n), dP(n) into P(n), dS(n), element i beside MFMA
-      // i / (16 / NA).
-      constexpr int NA = 2 * NK, EPM = 16 / NA;
-      auto nat_op = [&](int m) { return ld_nat((m & 1) ? On : Qn, nat[m >> 1]); };
+      // A(n): operand o (NA of them) feeds the two MFMAs (key tiles) of S(n+1)
+      // (o even) or dP(n+1) (o odd); it is read four operands ahead.  The VALU
+      // turns the 16 elements of S(n), dP(n) into P(n), dS(n) (key tile by key
+      // tile), element i beside operand i / (16 / NA).
+      constexpr int NA = 4 * NK, EPM = 16 / NA;
       bf16x8 op[NA];
 #pragma unroll
-      for (int m = 0; m < 4; ++m) op[m] = kEarlyA ? opn[m] : nat_op(m);
-      // LSE2 of rows 8 k + 4 g .. + 3 (group k of four elements), loaded
-      // kLdAhead groups before its use.
-      float4 lgk[4];
-      auto ld_group = [&](int k) { lgk[k] = *reinterpret_cast<const float4*>(ld + 8 * k + 4 * g); };
-#pragma unroll
-      for (int k = 0; k <= kLdAhead && k < 4; ++k) ld_group(k);
+      for (int o = 0; o < 4; ++o) op[o] = opn[o];
       float p[16], ds[16];
+      uint32_t pk[4][4];  // P and dS of key tile 0, then 1, packed in pairs
       bf16x8 pb[2], dsb[2];
-      // B(n): MFMA jj is dV (jj even) or dK (jj odd) for k-half hh, d-block
-      // db; its transposed operand is read three slots ahead (the first
-      // three in the last MFMA slots of A(n), which read nothing else).
-      constexpr int NB = 4 * ND;
-      auto tr_op = [&](int jj) {
-        const int blk = jj >> 1;
-        return tr_rd((jj & 1) ? Qc : Oc, blk / ND, blk % ND);
-      };
+      // B(n): operand jj feeds the two MFMAs of dV (jj even) or dK (jj odd) for
+      // d tile jj / 2; it is read three operands ahead (the first three in the
+      // last slots of A(n), which read nothing else).
+      constexpr int NB = 2 * ND;
+      auto tr_op = [&](int jj) { return tr_rd((jj & 1) ? Qc : Oc, jj >> 1); };
       bf16x8 top[NB];
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        if (i % EPM == 0) {
-          const int mi = i / EPM;
-          if (mi & 1) {
-            dnext = mfma32(op[mi], vf[mi >> 1], dnext);
-          } else {
-            snext = mfma32(op[mi], kf[mi >> 1], mi == 0 ? f32x16{} : snext);
-          }
-          if (mi + 4 < NA) op[mi + 4] = nat_op(mi + 4);
-          else if (kEarlyTr && mi + 4 - NA < 3) top[mi + 4 - NA] = tr_op(mi + 4 - NA);
-        }
-        const int e = i & 3;
-        const float4 l4 = lgk[i >> 2];
-        const float lv = e == 0 ? l4.x : e == 1 ? l4.y : e == 2 ? l4.z : l4.w;
+        const int o = i / EPM;
+        auto a_mfma = [&](int kt) {
+          const int kk = o >> 2, qt = (o >> 1) & 1;
+          if (o & 1) dnext.x[qt][kt] = mfma16(op[o], vf[kt][kk], kk == 0 ? nd[qt] : dnext.x[qt][kt]);
+          else snext.x[qt][kt] = mfma16(op[o], kf[kt][kk], kk == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : snext.x[qt][kt]);
+        };
+        if (i % EPM == 0) a_mfma(0);
+        __builtin_amdgcn_sched_barrier(0);
         // Element i's exp, element i-1's dS: an exp's result is not read by the
         // next instruction (that would cost a wait state).
-        p[i] = fast_exp2(scur[i] * C - lv);
-        if (i > 0) ds[i - 1] = p[i - 1] * dcur[i - 1];
-        if (e == 3 && i < 15) {  // rows 8 (v/4) + 4 g + v%4 of the next group of four
-          if ((i >> 2) + kLdAhead + 1 < 4) ld_group((i >> 2) + kLdAhead + 1);
+        const int kt = i >> 3, qt = (i >> 2) & 1, v = i & 3;
+        p[i] = fast_exp2(scur.x[qt][kt][v] * C - lg[qt][v]);
+        if (i % EPM == EPM / 2) {
+          __builtin_amdgcn_sched_barrier(0);
+          a_mfma(1);
+          __builtin_amdgcn_sched_barrier(0);
+          if (o + 4 < NA) op[o + 4] = nat_of(Qn, On, o + 4);
+          else if (o + 4 - NA < 3) top[o + 4 - NA] = tr_op(o + 4 - NA);
         }
-        if (i == 8) {
-          pb[0] = pack_bf16x8(p[0], p[1], p[2], p[3], p[4], p[5], p[6], p[7]);
-          dsb[0] = pack_bf16x8(ds[0], ds[1], ds[2], ds[3], ds[4], ds[5], ds[6], ds[7]);
+        if (i > 0) ds[i - 1] = p[i - 1] * dcur.x[((i - 1) >> 2) & 1][(i - 1) >> 3][(i - 1) & 3];
+        if (i >= 8 && i < 12) {  // P and dS of key tile 0 to bf16, two elements of each a slot
+          const int e = 2 * (i - 8);
+          pk[0][i - 8] = pack_bf16x2(p[e], p[e + 1]);
+          pk[1][i - 8] = pack_bf16x2(ds[e], ds[e + 1]);
+        }
+        if (i >= 12) {
+          const int e = 8 + 2 * (i - 12);
+          if (e + 1 < i) pk[2][i - 12] = pack_bf16x2(p[e], p[e + 1]);
+          if (e + 1 < i) pk[3][i - 12] = pack_bf16x2(ds[e], ds[e + 1]);
         }
         if (i % EPM == EPM - 1) __builtin_amdgcn_sched_barrier(0);
       }
-      ds[15] = p[15] * dcur[15];
-      pb[1] = pack_bf16x8(p[8], p[9], p[10], p[11], p[12], p[13], p[14], p[15]);
-      dsb[1] = pack_bf16x8(ds[8], ds[9], ds[10], ds[11], ds[12], ds[13], ds[14], ds[15]);
-      if (!kEarlyTr) {
-        top[0] = tr_op(0);
-        top[1] = tr_op(1);
-        top[2] = tr_op(2);
-      }
+      pb[0] = as_bf16x8(u32x4{pk[0][0], pk[0][1], pk[0][2], pk[0][3]});
+      dsb[0] = as_bf16x8(u32x4{pk[1][0], pk[1][1], pk[1][2], pk[1][3]});
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int jj = 0; jj < NB; ++jj) {
-        const int blk = jj >> 1, hh = blk / ND, db = blk % ND;
-        if (jj & 1) {
-          dk[db] = mfma32(dsb[hh], top[jj], dk[db]);
-        } else {
-          dv[db] = mfma32(pb[hh], top[jj], dv[db]);
+        const int dt = jj >> 1;
+        auto b_mfma = [&](int kt) {
+          if (jj & 1) dk[dt][kt] = mfma16(top[jj], dsb[kt], dk[dt][kt]);
+          else dv[dt][kt] = mfma16(top[jj], pb[kt], dv[dt][kt]);
+        };
+        b_mfma(0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (jj == 0) {  // the rest of key tile 1
+          pk[2][3] = pack_bf16x2(p[14], p[15]);
+          pb[1] = as_bf16x8(u32x4{pk[2][0], pk[2][1], pk[2][2], pk[2][3]});
+          ds[15] = p[15] * dcur.x[1][1][3];
         }
+        if (jj == 1) {
+          pk[3][3] = pack_bf16x2(ds[14], ds[15]);
+          dsb[1] = as_bf16x8(u32x4{pk[3][0], pk[3][1], pk[3][2], pk[3][3]});
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        b_mfma(1);
+        __builtin_amdgcn_sched_barrier(0);
         if (jj + 3 < NB) {
           top[jj + 3] = tr_op(jj + 3);
-        } else if (kEarlyA) {  // A(n+1)'s first natural operands and -Delta, from sub-block n+2
+        } else {  // A(n+1)'s first natural operands and -Delta, from sub-block n+2; LSE2 of n+1
           const int m0 = jj + 3 - NB;
-          opn[m0] = ld_nat((m0 & 1) ? obuf(IC<I2>{}) : qbuf(IC<I2>{}), nat[m0 >> 1]);
+          opn[m0] = nat_of(qbuf(IC<I2>{}), obuf(IC<I2>{}), m0);
+          if (m0 < 2) lg[m0] = rec_rd(lbuf(IC<I1>{}), m0);
           if (m0 == 2) {
-            opn[3] = ld_nat(obuf(IC<I2>{}), nat[1]);
-            dcur = ndelta(lbuf(IC<I2>{}));
+            opn[3] = nat_of(qbuf(IC<I2>{}), obuf(IC<I2>{}), 3);
+            nd[0] = rec_rd(lbuf(IC<I2>{}) + 32, 0);
+            nd[1] = rec_rd(lbuf(IC<I2>{}) + 32, 1);
           }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -445,73 +456,51 @@ __global__ __launch_bounds__(256, 1) void bwd_dkdv_bf16_kernel(ChunkArgs a) {
     // Past the last sub-block A still computes S, dP of the (zero) next slot;
     // they are never used.
     for (int n = 0; n < N; n += kRing) {
-      step(n, IC<0>{}, sa, da, sb2, db2);
+      step(IC<0>{}, sa, da, sb2, db2);
       if (n + 1 >= N) break;
-      step(n + 1, IC<1>{}, sb2, db2, sa, da);
+      step(IC<1>{}, sb2, db2, sa, da);
       if (n + 2 >= N) break;
-      step(n + 2, IC<2>{}, sa, da, sb2, db2);
+      step(IC<2>{}, sa, da, sb2, db2);
       if (n + 3 >= N) break;
-      step(n + 3, IC<3>{}, sb2, db2, sa, da);
+      step(IC<3>{}, sb2, db2, sa, da);
       if (n + 4 >= N) break;
-      step(n + 4, IC<4>{}, sa, da, sb2, db2);
+      step(IC<4>{}, sa, da, sb2, db2);
       if (n + 5 >= N) break;
-      step(n + 5, IC<5>{}, sb2, db2, sa, da);
+      step(IC<5>{}, sb2, db2, sa, da);
     }
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));  // no LDS-DMA in flight past the stream
   }
 
-  // Write back rows [k0, k0+128) n [kv0, kv1): lane <-> d, v <-> key.  In
-  // accumulate mode the 32 old values of a d-block are loaded before any of
-  // them is stored (dK and dV are distinct buffers, which the C ABI checks),
-  // so the loads share one memory round trip instead of one each (the sum
-  // is old + dK * scale in one fused multiply-add).  A block
-  // whose 128 keys are all in range (every one but a ragged last) takes a
-  // branch-free path: key v of the lane sits a compile-time number of rows
-  // past the lane's first key.
+  // Write back rows [k0, k0+128) n [kv0, kv1): lane <-> key, 16 bytes of d
+  // per access.  In accumulate mode a key tile's old values are all loaded
+  // before any is stored (dK and dV are distinct buffers, which the C ABI
+  // checks), so the loads share one memory round trip (the sum is old + dK *
+  // scale in one fused multiply-add).
   float* __restrict__ gdk = a.dk;
   float* __restrict__ gdv = a.dv;
-  const int64_t rs = (int64_t)a.Hkv * D;  // elements between consecutive keys
-  const int64_t key0 = k0 + 32 * w + 4 * g;
-  const int64_t base = ((b * a.S + key0) * a.Hkv + hk) * D + l32;
-  auto koff = [](int v) { return 8 * (v / 4) + (v % 4); };
-  if (k0 + 128 <= kv1) {
 #pragma unroll
-    for (int db = 0; db < ND; ++db) {
-      float* pk = gdk + base + 32 * db;
-      float* pv = gdv + base + 32 * db;
-      float ok[16], ov[16];
+  for (int kt = 0; kt < 2; ++kt) {
+    const int64_t jk = j + 16 * kt;
+    if (jk < kv1) {
+      const int64_t base = ((b * a.S + jk) * a.Hkv + hk) * D + 4 * g;
+      f32x4 ok[ND], ov[ND];
       if (a.accumulate) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          ok[v] = pk[koff(v) * rs];
-          ov[v] = pv[koff(v) * rs];
+        for (int dt = 0; dt < ND; ++dt) {
+          ok[dt] = *reinterpret_cast<const f32x4*>(gdk + base + 16 * dt);
+          ov[dt] = *reinterpret_cast<const f32x4*>(gdv + base + 16 * dt);
         }
       }
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        pk[koff(v) * rs] = a.accumulate ? __builtin_fmaf(dk[db][v], a.scale, ok[v]) : dk[db][v] * a.scale;
-        pv[koff(v) * rs] = a.accumulate ? ov[v] + dv[db][v] : dv[db][v];
-      }
-    }
-  } else {
+      for (int dt = 0; dt < ND; ++dt) {
+        f32x4 xk, xv;
 #pragma unroll
-    for (int db = 0; db < ND; ++db) {
-      float ok[16], ov[16];
-      if (a.accumulate) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int64_t idx = base + koff(v) * rs + 32 * db;
-          ok[v] = key0 + koff(v) < kv1 ? gdk[idx] : 0.f;
-          ov[v] = key0 + koff(v) < kv1 ? gdv[idx] : 0.f;
+        for (int v = 0; v < 4; ++v) {
+          xk[v] = a.accumulate ? __builtin_fmaf(dk[dt][kt][v], a.scale, ok[dt][v]) : dk[dt][kt][v] * a.scale;
+          xv[v] = a.accumulate ? ov[dt][v] + dv[dt][kt][v] : dv[dt][kt][v];
         }
-      }
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        if (key0 + koff(v) < kv1) {
-          const int64_t idx = base + koff(v) * rs + 32 * db;
-          gdk[idx] = a.accumulate ? __builtin_fmaf(dk[db][v], a.scale, ok[v]) : dk[db][v] * a.scale;
-          gdv[idx] = a.accumulate ? ov[v] + dv[db][v] : dv[db][v];
-        }
+        *reinterpret_cast<f32x4*>(gdk + base + 16 * dt) = xk;
+        *reinterpret_cast<f32x4*>(gdv + base + 16 * dt) = xv;
       }
     }
   }
@@ -530,8 +519,8 @@ __global__ __launch_bounds__(256, 1) void bwd_dkdv_bf16_kernel(ChunkArgs a) {
 // --------------------------------------------------------------------- dQ
 template <int D>
 __global__ __launch_bounds__(256, 1) void bwd_dq_bf16_kernel(ChunkArgs a) {
-  using T = XTile<D>;
-  constexpr int P = T::P, NK = D / 16, ND = D / 32;
+  using T = Tile<D>;
+  constexpr int P = T::P, NK = D / 32, ND = D / 16;  // k-steps of S and dP, d tiles
   constexpr int IPWK = (kSB / T::RPI) / 4;  // DMA instructions per wave per tensor per sub-block
   static_assert(IPWK >= 1 && IPWK * 4 * T::RPI == kSB, "sub-block splits over 4 waves");
   constexpr int DMA_PER_SB = 2 * IPWK;
@@ -548,7 +537,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_bf16_kernel(ChunkArgs a) {
   };
 
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l32 = lane & 31, g = lane >> 5;
+  const int l16 = lane & 15, g = lane >> 4;
   const GridPos gp = xcd_grouped();  // the query tiles of a head behind one L2
   const int t = gridDim.x - 1 - gp.x;  // longest (latest) query tiles first
   const int h = gp.y;
@@ -556,8 +545,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_bf16_kernel(ChunkArgs a) {
   const int hk = h / (a.Hq / a.Hkv);
   const int64_t c0 = a.c0, c1 = a.c1, s = c1 - c0;
   const int64_t q0 = c0 + (int64_t)t * kDqRows;
-  const int64_t r = q0 + 32 * w + l32;
-  const bool rvalid = r < c1;
+  const int64_t r = q0 + 32 * w + l16;  // this lane's rows: r and r + 16
   const int64_t kend = (q0 + kDqRows < c1) ? q0 + kDqRows : c1;
   const int nsub = (int)((kend + kSB - 1) / kSB);
   const int N = (int)(q0 / kSB);  // key sub-blocks every row of the workgroup sees in full
@@ -565,13 +553,10 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_bf16_kernel(ChunkArgs a) {
 
   int nat[NK];
 #pragma unroll
-  for (int kk = 0; kk < NK; ++kk) nat[kk] = T::nat(lane, kk);
-  int tro[ND][2];
+  for (int kk = 0; kk < NK; ++kk) nat[kk] = T::nat(lane, kk, 0);
+  int tro[ND];
 #pragma unroll
-  for (int db = 0; db < ND; ++db) {
-    tro[db][0] = T::tr(lane, db, 0);
-    tro[db][1] = T::tr(lane, db, 1);
-  }
+  for (int dt = 0; dt < ND; ++dt) tro[dt] = T::tr(lane, dt);
   const int64_t kvstride = (int64_t)a.Hkv * D;
   int dmak[IPWK];
 #pragma unroll
@@ -579,31 +564,34 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_bf16_kernel(ChunkArgs a) {
   const uint16_t* kbase = static_cast<const uint16_t*>(a.k) + (b * a.S * a.Hkv + hk) * D;
   const uint16_t* vbase = static_cast<const uint16_t*>(a.v) + (b * a.S * a.Hkv + hk) * D;
 
-  bf16x8 qf[NK], df[NK];
-  float lse2 = INFINITY, ndl = 0.f;  // a padding row gets P = 0
-  if (rvalid) {
-    const int64_t off = ((b * s + (r - c0)) * a.Hq + h) * D;
-    const uint16_t* qrow = static_cast<const uint16_t*>(a.q) + off;
-    const uint16_t* drow = static_cast<const uint16_t*>(a.dout) + off;
+  bf16x8 qf[2][NK], df[2][NK];
+  float lse2[2];
+  f32x4 ninit[2];  // -Delta of the row: the initial value of each dP^T accumulator, so the MFMAs produce dP^T - Delta
 #pragma unroll
-    for (int kk = 0; kk < NK; ++kk) {
-      qf[kk] = as_bf16x8(ld_global16(qrow + 16 * kk + 8 * g));
-      df[kk] = as_bf16x8(ld_global16(drow + 16 * kk + 8 * g));
+  for (int qt = 0; qt < 2; ++qt) {
+    const int64_t rq = r + 16 * qt;
+    float ndl = 0.f;
+    lse2[qt] = INFINITY;  // a padding row gets P = 0
+    if (rq < c1) {
+      const int64_t off = ((b * s + (rq - c0)) * a.Hq + h) * D;
+      const uint16_t* qrow = static_cast<const uint16_t*>(a.q) + off;
+      const uint16_t* drow = static_cast<const uint16_t*>(a.dout) + off;
+#pragma unroll
+      for (int kk = 0; kk < NK; ++kk) {
+        qf[qt][kk] = as_bf16x8(ld_global16(qrow + 32 * kk + 8 * g));
+        df[qt][kk] = as_bf16x8(ld_global16(drow + 32 * kk + 8 * g));
+      }
+      lse2[qt] = a.lse2[(b * a.Hq + h) * s + (rq - c0)];
+      ndl = a.delta[(b * a.Hq + h) * s + (rq - c0)];
+    } else {
+#pragma unroll
+      for (int kk = 0; kk < NK; ++kk) qf[qt][kk] = df[qt][kk] = bf16x8{};
     }
-    lse2 = a.lse2[(b * a.Hq + h) * s + (r - c0)];
-    ndl = a.delta[(b * a.Hq + h) * s + (r - c0)];
-  } else {
-#pragma unroll
-    for (int kk = 0; kk < NK; ++kk) qf[kk] = df[kk] = bf16x8{};
+    ninit[qt] = f32x4{ndl, ndl, ndl, ndl};
   }
-  f32x16 dq[ND];
+  f32x4 dq[ND][2];  // dQ^T: [d tile][query tile]
 #pragma unroll
-  for (int db = 0; db < ND; ++db) dq[db] = f32x16{};
-  // -Delta of the lane's row in every element: the initial value of each dP^T
-  // accumulator, so the MFMAs produce dP^T - Delta.
-  f32x16 ninit;
-#pragma unroll
-  for (int v = 0; v < 16; ++v) ninit[v] = ndl;
+  for (int dt = 0; dt < ND; ++dt) dq[dt][0] = dq[dt][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // DMA of K/V sub-block u (keys [32u, 32u+32)) into a slot; keys past the
   // chunk end load zeros, so every call issues DMA_PER_SB instructions.
@@ -626,18 +614,23 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_bf16_kernel(ChunkArgs a) {
     va += sbb;
     remk -= kSB;
   };
-  auto tr_rd = [&](const uint16_t* X, int hh, int db) {
-    return ld_tr(X, tro[db][0] + 16 * hh * P, tro[db][1] + 16 * hh * P);
+  auto nat_rd = [&](const uint16_t* X, int t, int kk) { return ld_nat(X + 16 * t * P, nat[D == 64 ? kk ^ t : kk]); };
+  auto tr_rd = [&](const uint16_t* X, int dt) { return ld_tr(X, tro[dt], tro[D == 64 ? dt ^ 2 : dt] + 16 * P); };
+  // Natural operand o of a sub-block: k-step o / 4, key tile (o / 2) % 2, K (o even) or V (o odd).
+  auto nat_of = [&](const uint16_t* K, int o) { return nat_rd((o & 1) ? K + kSB * P : K, (o >> 1) & 1, o >> 2); };
+  // The MFMA of query tile qt that operand o feeds: S^T = K Q^T or dP^T - Delta = V dO^T - Delta (lane <-> query).
+  auto sdp_one = [&](const bf16x8& x, int o, int qt, S4& sv, S4& dp) {
+    const int kk = o >> 2, kt = (o >> 1) & 1;
+    if (o & 1) dp.x[kt][qt] = mfma16(x, df[qt][kk], kk == 0 ? ninit[qt] : dp.x[kt][qt]);
+    else sv.x[kt][qt] = mfma16(x, qf[qt][kk], kk == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : sv.x[kt][qt]);
   };
-  // S^T = K Q^T and dP^T - Delta = V dO^T - Delta of one sub-block (lane <-> query).
-  auto sdp = [&](const uint16_t* K, f32x16& sv, f32x16& dp) {
-    const uint16_t* V = K + kSB * P;
-    sv = mfma32(ld_nat(K, nat[0]), qf[0], f32x16{});
-    dp = mfma32(ld_nat(V, nat[0]), df[0], ninit);
+  constexpr int NA = 4 * NK;
+  auto sdp = [&](const uint16_t* K, S4& sv, S4& dp) {
 #pragma unroll
-    for (int kk = 1; kk < NK; ++kk) {
-      sv = mfma32(ld_nat(K, nat[kk]), qf[kk], sv);
-      dp = mfma32(ld_nat(V, nat[kk]), df[kk], dp);
+    for (int o = 0; o < NA; ++o) {
+      const bf16x8 x = nat_of(K, o);
+      sdp_one(x, o, 0, sv, dp);
+      sdp_one(x, o, 1, sv, dp);
     }
   };
 
@@ -650,98 +643,97 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_bf16_kernel(ChunkArgs a) {
   issue_next(R4);
 
   if (N > 0) {
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm((kAhead - (kEarlyAq ? 2 : 1)) * DMA_PER_SB));
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm((kAhead - 2) * DMA_PER_SB));
     __syncthreads();
-    f32x16 sa, da, sb2, db2;
+    S4 sa, da, sb2, db2;
     sdp(R0, sa, da);
     bf16x8 opn[4];
-    if (kEarlyAq) {
 #pragma unroll
-      for (int m = 0; m < 4; ++m) opn[m] = ld_nat((m & 1) ? R1 + kSB * P : R1, nat[m >> 1]);
-    }
+    for (int o = 0; o < 4; ++o) opn[o] = nat_of(R1, o);
     // Step n in slot I: A(n) reads slot I+1 (natural K, V); B(n) reads slot I
-    // (transposed K) and, in its last MFMA slots, A(n+1)'s first natural
-    // operands from slot I+2.  At its start sub-blocks n+1 and n+2 have
-    // landed; then sub-block n+5 goes to slot I+5 = I-1, free since step n-1.
-    auto step = [&](int n, auto sl, f32x16& scur, f32x16& dcur, f32x16& snext, f32x16& dnext) {
+    // (transposed K) and, in its last slots, A(n+1)'s first natural operands
+    // from slot I+2.  At its start sub-blocks n+1 and n+2 have landed; then
+    // sub-block n+5 goes to slot I+5 = I-1, free since step n-1.
+    auto step = [&](auto sl, S4& scur, S4& dcur, S4& snext, S4& dnext) {
       constexpr int I = decltype(sl)::value;
       constexpr int I1 = (I + 1) % kRing, I2 = (I + 2) % kRing, I5 = (I + kAhead) % kRing;
-      __builtin_amdgcn_s_waitcnt(waitcnt_vm((kAhead - (kEarlyAq ? 3 : 2)) * DMA_PER_SB));
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm((kAhead - 3) * DMA_PER_SB));
       __syncthreads();
       issue_next(slot(IC<I5>{}));  // sub-block n + kAhead
       const uint16_t* Kn = slot(IC<I1>{});
-      const uint16_t* Vn = Kn + kSB * P;
       const uint16_t* Kc = slot(IC<I>{});
-      // A(n): MFMA m (NA of them) is S^T(n+1) (m even) or dP^T(n+1) (m odd),
-      // k-step m/2; its operand is read four MFMAs ahead.  The VALU turns the
-      // 16 elements of S^T(n), dP^T(n) into dS^T(n), element i beside MFMA
-      // i / (16 / NA).
-      constexpr int NA = 2 * NK, EPM = 16 / NA;
-      auto nat_op = [&](int m) { return ld_nat((m & 1) ? Vn : Kn, nat[m >> 1]); };
+      // A(n): operand o (NA of them) feeds two MFMAs of S^T(n+1) or dP^T(n+1);
+      // it is read four operands ahead.  The VALU turns the 16 elements of
+      // S^T(n), dP^T(n) into dS^T(n) (query tile by query tile), element i
+      // beside operand i / (16 / NA).
+      constexpr int EPM = 16 / NA;
       bf16x8 op[NA];
 #pragma unroll
-      for (int m = 0; m < 4; ++m) op[m] = kEarlyAq ? opn[m] : nat_op(m);
+      for (int o = 0; o < 4; ++o) op[o] = opn[o];
       float pv[16], ds[16];
+      uint32_t pk[2][4];  // dS of query tile 0, then 1, packed in pairs
       bf16x8 dsb[2];
-      // B(n): MFMA jj is dQ^T d-block jj % ND for k-half jj / ND; its
-      // transposed K operand is read three slots ahead (the first three in
-      // the last MFMA slots of A(n)).
-      constexpr int NB = 2 * ND;
-      auto tr_op = [&](int jj) { return tr_rd(Kc, jj / ND, jj % ND); };
+      // B(n): operand jj feeds the two MFMAs of dQ^T d tile jj; it is read three
+      // operands ahead (the first three in the last slots of A(n)).
+      constexpr int NB = ND;
       bf16x8 top[NB];
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        if (i % EPM == 0) {
-          const int mi = i / EPM;
-          if (mi & 1) {
-            dnext = mfma32(op[mi], df[mi >> 1], mi == 1 ? ninit : dnext);
-          } else {
-            snext = mfma32(op[mi], qf[mi >> 1], mi == 0 ? f32x16{} : snext);
-          }
-          if (mi + 4 < NA) op[mi + 4] = nat_op(mi + 4);
-          else if (kEarlyTr && mi + 4 - NA < 3) top[mi + 4 - NA] = tr_op(mi + 4 - NA);
-        }
+        const int o = i / EPM;
+        if (i % EPM == 0) sdp_one(op[o], o, 0, snext, dnext);
+        __builtin_amdgcn_sched_barrier(0);
         // Element i's exp, element i-1's dS (no exp result read right away).
-        pv[i] = fast_exp2(scur[i] * C - lse2);
-        if (i > 0) ds[i - 1] = pv[i - 1] * dcur[i - 1];
-        if (i == 8) dsb[0] = pack_bf16x8(ds[0], ds[1], ds[2], ds[3], ds[4], ds[5], ds[6], ds[7]);
+        const int qt = i >> 3, kt = (i >> 2) & 1, v = i & 3;
+        pv[i] = fast_exp2(scur.x[kt][qt][v] * C - lse2[qt]);
+        if (i % EPM == EPM / 2) {
+          __builtin_amdgcn_sched_barrier(0);
+          sdp_one(op[o], o, 1, snext, dnext);
+          __builtin_amdgcn_sched_barrier(0);
+          if (o + 4 < NA) op[o + 4] = nat_of(Kn, o + 4);
+          else if (o + 4 - NA < 3) top[o + 4 - NA] = tr_rd(Kc, o + 4 - NA);
+        }
+        if (i > 0) ds[i - 1] = pv[i - 1] * dcur.x[((i - 1) >> 2) & 1][(i - 1) >> 3][(i - 1) & 3];
+        if (i >= 8 && i < 12) pk[0][i - 8] = pack_bf16x2(ds[2 * (i - 8)], ds[2 * (i - 8) + 1]);
+        if (i >= 12 && 8 + 2 * (i - 12) + 1 < i) pk[1][i - 12] = pack_bf16x2(ds[8 + 2 * (i - 12)], ds[9 + 2 * (i - 12)]);
         if (i % EPM == EPM - 1) __builtin_amdgcn_sched_barrier(0);
       }
-      ds[15] = pv[15] * dcur[15];
-      dsb[1] = pack_bf16x8(ds[8], ds[9], ds[10], ds[11], ds[12], ds[13], ds[14], ds[15]);
-      if (!kEarlyTr) {
-        top[0] = tr_op(0);
-        top[1] = tr_op(1);
-        top[2] = tr_op(2);
-      }
+      dsb[0] = as_bf16x8(u32x4{pk[0][0], pk[0][1], pk[0][2], pk[0][3]});
+      ds[15] = pv[15] * dcur.x[1][1][3];
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int jj = 0; jj < NB; ++jj) {
-        dq[jj % ND] = mfma32(top[jj], dsb[jj / ND], dq[jj % ND]);
+        dq[jj][0] = mfma16(top[jj], dsb[0], dq[jj][0]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (jj == 0) {
+          pk[1][3] = pack_bf16x2(ds[14], ds[15]);
+          dsb[1] = as_bf16x8(u32x4{pk[1][0], pk[1][1], pk[1][2], pk[1][3]});
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        dq[jj][1] = mfma16(top[jj], dsb[1], dq[jj][1]);
+        __builtin_amdgcn_sched_barrier(0);
         if (jj + 3 < NB) {
-          top[jj + 3] = tr_op(jj + 3);
-        } else if (kEarlyAq) {  // A(n+1)'s first natural operands, from sub-block n+2
-          const uint16_t* K2 = slot(IC<I2>{});
+          top[jj + 3] = tr_rd(Kc, jj + 3);
+        } else {  // A(n+1)'s first natural operands, from sub-block n+2
           const int m0 = jj + 3 - NB;
-          opn[m0] = ld_nat((m0 & 1) ? K2 + kSB * P : K2, nat[m0 >> 1]);
-          if (m0 == 2) opn[3] = ld_nat(K2 + kSB * P, nat[1]);
+          opn[m0] = nat_of(slot(IC<I2>{}), m0);
+          if (m0 == 2) opn[3] = nat_of(slot(IC<I2>{}), 3);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
     };
     for (int n = 0; n < N; n += kRing) {
-      step(n, IC<0>{}, sa, da, sb2, db2);
+      step(IC<0>{}, sa, da, sb2, db2);
       if (n + 1 >= N) break;
-      step(n + 1, IC<1>{}, sb2, db2, sa, da);
+      step(IC<1>{}, sb2, db2, sa, da);
       if (n + 2 >= N) break;
-      step(n + 2, IC<2>{}, sa, da, sb2, db2);
+      step(IC<2>{}, sa, da, sb2, db2);
       if (n + 3 >= N) break;
-      step(n + 3, IC<3>{}, sb2, db2, sa, da);
+      step(IC<3>{}, sb2, db2, sa, da);
       if (n + 4 >= N) break;
-      step(n + 4, IC<4>{}, sa, da, sb2, db2);
+      step(IC<4>{}, sa, da, sb2, db2);
       if (n + 5 >= N) break;
-      step(n + 5, IC<5>{}, sb2, db2, sa, da);
+      step(IC<5>{}, sb2, db2, sa, da);
     }
   }
 
@@ -751,35 +743,428 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_bf16_kernel(ChunkArgs a) {
   __syncthreads();
   for (int u = N; u < nsub; ++u) {
     const uint16_t* K = slot_rt(u % kRing);
-    f32x16 sv, dp;
+    S4 sv, dp;
     sdp(K, sv, dp);
-    const int rel = (int)(r - (int64_t)u * kSB);  // keys past this row are masked
-    float ds[16];
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      float p = fast_exp2(sv[v] * C - lse2);
-      if (8 * (v / 4) + 4 * g + (v % 4) > rel) p = 0.f;
-      ds[v] = p * dp[v];
-    }
+    const int rel = (int)(r - (int64_t)u * kSB);  // keys past row r are masked
     bf16x8 dsb[2];
-    dsb[0] = pack_bf16x8(ds[0], ds[1], ds[2], ds[3], ds[4], ds[5], ds[6], ds[7]);
-    dsb[1] = pack_bf16x8(ds[8], ds[9], ds[10], ds[11], ds[12], ds[13], ds[14], ds[15]);
 #pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
+    for (int qt = 0; qt < 2; ++qt) {
+      float ds[8];
 #pragma unroll
-      for (int db = 0; db < ND; ++db) dq[db] = mfma32(tr_rd(K, hh, db), dsb[hh], dq[db]);
+      for (int e = 0; e < 8; ++e) {
+        const int kt = e >> 2, v = e & 3;
+        float p = fast_exp2(sv.x[kt][qt][v] * C - lse2[qt]);
+        if (16 * kt + 4 * g + v > rel + 16 * qt) p = 0.f;
+        ds[e] = p * dp.x[kt][qt][v];
+      }
+      dsb[qt] = pack_bf16x8(ds[0], ds[1], ds[2], ds[3], ds[4], ds[5], ds[6], ds[7]);
+    }
+#pragma unroll
+    for (int dt = 0; dt < ND; ++dt) {
+      const bf16x8 kx = tr_rd(K, dt);
+#pragma unroll
+      for (int qt = 0; qt < 2; ++qt) dq[dt][qt] = mfma16(kx, dsb[qt], dq[dt][qt]);
     }
   }
 
-  if (rvalid) {
-    uint16_t* qrow = static_cast<uint16_t*>(a.dq) + ((b * s + (r - c0)) * a.Hq + h) * D;
 #pragma unroll
-    for (int db = 0; db < ND; ++db) {
+  for (int qt = 0; qt < 2; ++qt) {
+    const int64_t rq = r + 16 * qt;
+    if (rq < c1) {
+      uint16_t* qrow = static_cast<uint16_t*>(a.dq) + ((b * s + (rq - c0)) * a.Hq + h) * D;
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        *reinterpret_cast<u32x2*>(qrow + 32 * db + 8 * q4 + 4 * g) =
-            pack_bf16x4(dq[db][4 * q4 + 0] * a.scale, dq[db][4 * q4 + 1] * a.scale,
-                        dq[db][4 * q4 + 2] * a.scale, dq[db][4 * q4 + 3] * a.scale);
+      for (int dt = 0; dt < ND; ++dt)
+        *reinterpret_cast<u32x2*>(qrow + 16 * dt + 4 * g) =
+            pack_bf16x4(dq[dt][qt][0] * a.scale, dq[dt][qt][1] * a.scale, dq[dt][qt][2] * a.scale,
+                        dq[dt][qt][3] * a.scale);
+    }
+  }
+}
+
+// dQ for grids that leave compute units idle: a workgroup is 8 waves, two groups
+// of 32 query rows of one head times four parts of the keys (part ks has the
+// 32-key sub-blocks u = ks, ks + 4, ...); the parts are added through LDS in
+// part order.  A sub-block's part depends on its position in the sequence
+// alone, so a row's result does not depend on the chunking.
+template <int D>
+__global__ __launch_bounds__(512) void bwd_dq_split_kernel(ChunkArgs a) {
+  using T = Tile<D>;
+  constexpr int P = T::P, NK = D / 32, ND = D / 16, RG = 2, KS = 4, R = 32 * RG;
+  constexpr int IPW = 32 / T::RPI / RG;  // DMA instructions per wave for each of K and V
+  constexpr int SB = 2 * kSB * P;        // elements of a sub-block's K and V
+  constexpr int OP = D + 4;              // row pitch of the partial dQ's, floats
+  constexpr int kBytes = 2 * KS * SB * 2 > KS * R * OP * 4 ? 2 * KS * SB * 2 : KS * R * OP * 4;
+  __shared__ __attribute__((aligned(1024))) unsigned char mem[kBytes];
+
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, g = lane >> 4, rg = w % RG, ks = w / RG;
+  const GridPos gp = xcd_grouped();
+  const int h = gp.y;
+  const int64_t b = gp.z;
+  const int hk = h / (a.Hq / a.Hkv);
+  const int64_t c0 = a.c0, c1 = a.c1, s = c1 - c0;
+  const int64_t q0 = c0 + (int64_t)(gridDim.x - 1 - gp.x) * R;
+  const int64_t qw = q0 + 32 * rg, r = qw + l16;  // this lane's rows: r and r + 16
+  const int64_t kend = q0 + R < c1 ? q0 + R : c1;
+  const int nsub = (int)((kend + kSB - 1) / kSB), nstep = (nsub + KS - 1) / KS;
+  const float C = a.scale * kLog2e;
+
+  int nat[NK], tro[ND];
+#pragma unroll
+  for (int kk = 0; kk < NK; ++kk) nat[kk] = T::nat(lane, kk, 0);
+#pragma unroll
+  for (int dt = 0; dt < ND; ++dt) tro[dt] = T::tr(lane, dt);
+  const int64_t kvstride = (int64_t)a.Hkv * D;
+  int dma[IPW];
+#pragma unroll
+  for (int x = 0; x < IPW; ++x) dma[x] = T::dma(lane, rg * IPW + x, kvstride);
+  bf16x8 qf[2][NK], df[2][NK];
+  float lse2[2];
+  f32x4 ninit[2];
+#pragma unroll
+  for (int qt = 0; qt < 2; ++qt) {
+    const int64_t rq = r + 16 * qt, rc = rq < c1 ? rq : c1 - 1;
+    const int64_t off = ((b * s + (rc - c0)) * a.Hq + h) * D;
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk) {
+      qf[qt][kk] = as_bf16x8(ld_global16(static_cast<const uint16_t*>(a.q) + off + 32 * kk + 8 * g));
+      df[qt][kk] = as_bf16x8(ld_global16(static_cast<const uint16_t*>(a.dout) + off + 32 * kk + 8 * g));
+    }
+    lse2[qt] = rq < c1 ? a.lse2[(b * a.Hq + h) * s + (rc - c0)] : INFINITY;  // a padding row gets P = 0
+    const float ndl = a.delta[(b * a.Hq + h) * s + (rc - c0)];
+    ninit[qt] = f32x4{ndl, ndl, ndl, ndl};
+  }
+  const uint16_t* kbase = static_cast<const uint16_t*>(a.k) + (b * a.S * a.Hkv + hk) * D;
+  const uint16_t* vbase = static_cast<const uint16_t*>(a.v) + (b * a.S * a.Hkv + hk) * D;
+  uint16_t* const kv = reinterpret_cast<uint16_t*>(mem) + ks * SB;  // this part's slot, buffer 0
+  auto issue = [&](int i) {  // keys past the chunk arrive as zeros
+    const int64_t j0 = ((int64_t)i * KS + ks) * kSB;
+    uint16_t* dst = kv + (i & 1) * KS * SB;
+    const auto rk = tile_rsrc(kbase + j0 * kvstride, c1 - j0, kSB, kvstride);
+    const auto rv = tile_rsrc(vbase + j0 * kvstride, c1 - j0, kSB, kvstride);
+#pragma unroll
+    for (int x = 0; x < IPW; ++x) {
+      lds_dma16(rk, dst + (rg * IPW + x) * 512, dma[x]);
+      lds_dma16(rv, dst + kSB * P + (rg * IPW + x) * 512, dma[x]);
+    }
+  };
+  f32x4 dq[ND][2];
+#pragma unroll
+  for (int dt = 0; dt < ND; ++dt) dq[dt][0] = dq[dt][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto block = [&](int u, const uint16_t* K) {
+    // Operands are read a few ahead of their MFMAs (left to the compiler, each
+    // read was waited for right after it was issued): o is k-step o / 4, key
+    // tile (o / 2) % 2, K (o even) or V (o odd).
+    constexpr int NA = 4 * NK, kNat = 6, kTr = 4;
+    bf16x8 op[NA], top[ND];
+    auto rd = [&](int o) {
+      const int kk = o >> 2, kt = (o >> 1) & 1;
+      return ld_nat(K + ((o & 1) ? kSB * P : 0) + 16 * kt * P, nat[D == 64 ? kk ^ kt : kk]);
+    };
+    auto rd_tr = [&](int dt) { return ld_tr(K, tro[dt], tro[D == 64 ? dt ^ 2 : dt] + 16 * P); };
+    S4 sv, dp;
+#pragma unroll
+    for (int o = 0; o < kNat; ++o) op[o] = rd(o);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int o = 0; o < NA; ++o) {
+      const int kk = o >> 2, kt = (o >> 1) & 1;
+#pragma unroll
+      for (int qt = 0; qt < 2; ++qt) {
+        if (o & 1) dp.x[kt][qt] = mfma16(op[o], df[qt][kk], kk == 0 ? ninit[qt] : dp.x[kt][qt]);
+        else sv.x[kt][qt] = mfma16(op[o], qf[qt][kk], kk == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : sv.x[kt][qt]);
+      }
+      if (o + kNat < NA) op[o + kNat] = rd(o + kNat);
+      else if (o + kNat - NA < kTr) top[o + kNat - NA] = rd_tr(o + kNat - NA);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    const int rel = (int)(r - (int64_t)u * kSB);  // keys past row r are masked
+    float p[2][8];
+#pragma unroll
+    for (int qt = 0; qt < 2; ++qt) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) p[qt][e] = fast_exp2(sv.x[e >> 2][qt][e & 3] * C - lse2[qt]);
+    }
+    if ((int64_t)u * kSB + kSB - 1 > qw) {
+#pragma unroll
+      for (int qt = 0; qt < 2; ++qt) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          if (16 * (e >> 2) + 4 * g + (e & 3) > rel + 16 * qt) p[qt][e] = 0.f;
+        }
+      }
+    }
+    bf16x8 dsb[2];
+#pragma unroll
+    for (int qt = 0; qt < 2; ++qt) {
+      float ds[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) ds[e] = p[qt][e] * dp.x[e >> 2][qt][e & 3];
+      dsb[qt] = pack_bf16x8(ds[0], ds[1], ds[2], ds[3], ds[4], ds[5], ds[6], ds[7]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int dt = 0; dt < ND; ++dt) {
+#pragma unroll
+      for (int qt = 0; qt < 2; ++qt) dq[dt][qt] = mfma16(top[dt], dsb[qt], dq[dt][qt]);
+      if (dt + kTr < ND) top[dt + kTr] = rd_tr(dt + kTr);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  issue(0);
+  for (int i = 0; i < nstep; ++i) {
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+    __syncthreads();  // step i landed; every wave is done with step i - 1
+    if (i + 1 < nstep) issue(i + 1);
+    const int u = i * KS + ks;
+    if ((int64_t)u * kSB <= qw + 31) block(u, kv + (i & 1) * KS * SB);  // else past this wave's rows
+  }
+
+  __syncthreads();
+  float* const os = reinterpret_cast<float*>(mem);  // [part][row][D], over the K/V slots
+#pragma unroll
+  for (int qt = 0; qt < 2; ++qt) {
+#pragma unroll
+    for (int dt = 0; dt < ND; ++dt)
+      *reinterpret_cast<f32x4*>(os + (ks * R + 32 * rg + 16 * qt + l16) * OP + 16 * dt + 4 * g) = dq[dt][qt];
+  }
+  __syncthreads();
+  constexpr int TPR = 512 / R, EPT = D / TPR;  // threads per row, elements per thread
+  const int row = tid / TPR, d0 = (tid % TPR) * EPT;
+  if (q0 + row >= c1) return;
+  uint16_t* qrow = static_cast<uint16_t*>(a.dq) + ((b * s + (q0 + row - c0)) * a.Hq + h) * D + d0;
+#pragma unroll
+  for (int e = 0; e < EPT; e += 4) {
+    f32x4 acc = *reinterpret_cast<const f32x4*>(os + row * OP + d0 + e);
+#pragma unroll
+    for (int x = 1; x < KS; ++x) acc += *reinterpret_cast<const f32x4*>(os + (x * R + row) * OP + d0 + e);
+    *reinterpret_cast<u32x2*>(qrow + e) =
+        pack_bf16x4(acc[0] * a.scale, acc[1] * a.scale, acc[2] * a.scale, acc[3] * a.scale);
+  }
+}
+
+// dK/dV for grids that leave compute units idle: KG groups of 32 keys of one KV
+// head times QS parts of the chunk's query sub-blocks (32 rows; sub-block n of
+// the group's head hh is number hh * nsb + n, and part qs has numbers qs, qs +
+// QS, ...); the parts are added through LDS in part order.  A sub-block's part
+// depends on its position in the chunk alone, so a key's sum does not depend on
+// the range of keys a launch covers.  D = 128: 4 waves, one per SIMD by their
+// accumulators and K/V fragments; D = 64: 8.
+template <int D, int KG, int QS>
+__global__ __launch_bounds__(64 * KG * QS) void bwd_dkdv_split_kernel(ChunkArgs a) {
+  using T = Tile<D>;
+  constexpr int P = T::P, NK = D / 32, ND = D / 16, NT = 64 * KG * QS, R = 32 * KG;
+  constexpr int IPW = 32 / T::RPI / KG;  // DMA instructions per wave for each of Q and dO
+  static_assert(IPW >= 1 && IPW * KG * T::RPI == 32, "a sub-block splits over KG waves");
+  constexpr int SB = 2 * kSB * P;  // elements of a sub-block's Q and dO
+  constexpr int OP = D + 4;        // row pitch of the partial sums, floats
+  constexpr int kBytes = 2 * QS * SB * 2 > QS * R * OP * 4 ? 2 * QS * SB * 2 : QS * R * OP * 4;
+  __shared__ __attribute__((aligned(1024))) unsigned char mem[kBytes];
+
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, g = lane >> 4, kg = w % KG, qs = w / KG;
+  const GridPos gp = xcd_grouped();
+  const int hk = gp.y, G = a.Hq / a.Hkv;
+  const int64_t b = gp.z;
+  const int64_t c0 = a.c0, c1 = a.c1, s = c1 - c0, kv1 = a.kv1;
+  const int64_t kw = a.kv0 + (int64_t)gp.x * R;  // the workgroup's first key
+  const int64_t k0 = kw + 32 * kg, j = k0 + l16;  // this lane's keys: j and j + 16
+  const float C = a.scale * kLog2e;
+  const int nsb = (int)((s + kSB - 1) / kSB);
+  const int sb_begin = kw > c0 ? (int)((kw - c0) / kSB) : 0;  // the first sub-block that sees a key here
+
+  int nat[NK], tro[ND];
+#pragma unroll
+  for (int kk = 0; kk < NK; ++kk) nat[kk] = T::nat(lane, kk, 0);
+#pragma unroll
+  for (int dt = 0; dt < ND; ++dt) tro[dt] = T::tr(lane, dt);
+  const int64_t qstride = (int64_t)a.Hq * D;
+  int dma[IPW];
+#pragma unroll
+  for (int x = 0; x < IPW; ++x) dma[x] = T::dma(lane, kg * IPW + x, qstride);
+  bf16x8 kf[2][NK], vf[2][NK];
+#pragma unroll
+  for (int kt = 0; kt < 2; ++kt) {
+    const int64_t jk = j + 16 * kt;
+    const int64_t off = ((b * a.S + jk) * a.Hkv + hk) * D;
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk) {
+      kf[kt][kk] = jk < kv1 ? as_bf16x8(ld_global16(static_cast<const uint16_t*>(a.k) + off + 32 * kk + 8 * g)) : bf16x8{};
+      vf[kt][kk] = jk < kv1 ? as_bf16x8(ld_global16(static_cast<const uint16_t*>(a.v) + off + 32 * kk + 8 * g)) : bf16x8{};
+    }
+  }
+  f32x4 dk[ND][2], dv[ND][2];  // dK^T, dV^T: [d tile][key tile]
+#pragma unroll
+  for (int dt = 0; dt < ND; ++dt) dk[dt][0] = dk[dt][1] = dv[dt][0] = dv[dt][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  // A step is QS consecutive numbers, the first being sub-block n of head hh;
+  // steps whose sub-blocks all lie before sb_begin are passed over.
+  struct Pos { int hh, n, i; };
+  const int total = (G * nsb + QS - 1) / QS;  // steps
+  auto settle = [&](Pos& p) {
+    for (;;) {
+      while (p.n >= nsb) {
+        p.n -= nsb;
+        ++p.hh;
+      }
+      if (p.n + QS - 1 >= sb_begin || p.i >= total) return;
+      p.n += QS;
+      ++p.i;
+    }
+  };
+  auto own = [&](Pos p) {  // this part's number of the step
+    p.n += qs;
+    while (p.n >= nsb) {
+      p.n -= nsb;
+      ++p.hh;
+    }
+    return p;
+  };
+  auto active = [&](const Pos& p) { return p.hh < G && p.n >= sb_begin; };
+  uint16_t* const slot = reinterpret_cast<uint16_t*>(mem) + qs * SB;  // this part's, buffer 0
+  f32x4 lg[2], nd[2], lgn[2], ndn[2];  // LSE2 and -Delta of rows 16 qt + 4 g + 0..3, this step's and the next's
+  auto issue = [&](const Pos& step, int buf) {
+    const Pos p = own(step);
+    const int64_t r0 = (int64_t)p.n * kSB;
+    const int h = hk * G + (p.hh < G ? p.hh : 0);
+    const int64_t valid = active(p) ? s - r0 : 0;
+    const int64_t tile0 = (b * s + r0) * a.Hq + h;
+    const auto rq = tile_rsrc(static_cast<const uint16_t*>(a.q) + tile0 * D, valid, kSB, qstride);
+    const auto ro = tile_rsrc(static_cast<const uint16_t*>(a.dout) + tile0 * D, valid, kSB, qstride);
+    uint16_t* dst = slot + buf * QS * SB;
+#pragma unroll
+    for (int x = 0; x < IPW; ++x) {
+      lds_dma16(rq, dst + (kg * IPW + x) * 512, dma[x]);
+      lds_dma16(ro, dst + kSB * P + (kg * IPW + x) * 512, dma[x]);
+    }
+    const int64_t rec = (b * a.Hq + h) * s;
+#pragma unroll
+    for (int qt = 0; qt < 2; ++qt) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int64_t rr = r0 + 16 * qt + 4 * g + v;
+        const bool ok = rr < s && p.hh < G;  // rows past the chunk: zeros
+        lgn[qt][v] = ok ? a.lse2[rec + rr] : 0.f;
+        ndn[qt][v] = ok ? a.delta[rec + rr] : 0.f;
+      }
+    }
+  };
+  auto block = [&](const Pos& p, const uint16_t* Qs) {
+    const uint16_t* Os = Qs + kSB * P;
+    // As in the split dQ kernel: natural operand o is k-step o / 4, row tile
+    // (o / 2) % 2, Q (o even) or dO (o odd); transposed operand jj is d tile
+    // jj / 2 of dO (jj even) or Q (jj odd).
+    constexpr int NA = 4 * NK, NB = 2 * ND, kNat = 6, kTr = 4;
+    bf16x8 op[NA], top[NB];
+    auto rd = [&](int o) {
+      const int kk = o >> 2, qt = (o >> 1) & 1;
+      return ld_nat(((o & 1) ? Os : Qs) + 16 * qt * P, nat[D == 64 ? kk ^ qt : kk]);
+    };
+    auto rd_tr = [&](int jj) {
+      const int dt = jj >> 1;
+      return ld_tr((jj & 1) ? Qs : Os, tro[dt], tro[D == 64 ? dt ^ 2 : dt] + 16 * P);
+    };
+    S4 sv, dp;
+#pragma unroll
+    for (int o = 0; o < kNat; ++o) op[o] = rd(o);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int o = 0; o < NA; ++o) {
+      const int kk = o >> 2, qt = (o >> 1) & 1;
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt) {
+        if (o & 1) dp.x[qt][kt] = mfma16(op[o], vf[kt][kk], kk == 0 ? nd[qt] : dp.x[qt][kt]);
+        else sv.x[qt][kt] = mfma16(op[o], kf[kt][kk], kk == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : sv.x[qt][kt]);
+      }
+      if (o + kNat < NA) op[o + kNat] = rd(o + kNat);
+      else if (o + kNat - NA < kTr) top[o + kNat - NA] = rd_tr(o + kNat - NA);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    const int64_t r0g = c0 + (int64_t)p.n * kSB;  // global row of the sub-block's first row
+    float pr[2][8];
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) pr[kt][e] = fast_exp2(sv.x[e >> 2][kt][e & 3] * C - lg[e >> 2][e & 3]);
+    }
+    if (k0 + 31 > r0g) {
+      const int rel = (int)(j - r0g);  // key j sees row r iff j <= r
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          if (rel + 16 * kt > 16 * (e >> 2) + 4 * g + (e & 3)) pr[kt][e] = 0.f;
+        }
+      }
+    }
+    bf16x8 pb[2], dsb[2];
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt) {
+      float ds[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) ds[e] = pr[kt][e] * dp.x[e >> 2][kt][e & 3];
+      pb[kt] = pack_bf16x8(pr[kt][0], pr[kt][1], pr[kt][2], pr[kt][3], pr[kt][4], pr[kt][5], pr[kt][6], pr[kt][7]);
+      dsb[kt] = pack_bf16x8(ds[0], ds[1], ds[2], ds[3], ds[4], ds[5], ds[6], ds[7]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int jj = 0; jj < NB; ++jj) {
+      const int dt = jj >> 1;
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt) {
+        if (jj & 1) dk[dt][kt] = mfma16(top[jj], dsb[kt], dk[dt][kt]);
+        else dv[dt][kt] = mfma16(top[jj], pb[kt], dv[dt][kt]);
+      }
+      if (jj + kTr < NB) top[jj + kTr] = rd_tr(jj + kTr);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  Pos cur{0, 0, 0};
+  settle(cur);
+  int buf = 0;
+  if (cur.i < total) issue(cur, 0);
+  while (cur.i < total) {
+    Pos nxt{cur.hh, cur.n + QS, cur.i + 1};
+    settle(nxt);
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+    __syncthreads();  // this step landed; every wave is done with the one before
+#pragma unroll
+    for (int qt = 0; qt < 2; ++qt) {
+      lg[qt] = lgn[qt];
+      nd[qt] = ndn[qt];
+    }
+    if (nxt.i < total) issue(nxt, buf ^ 1);
+    const Pos p = own(cur);
+    if (active(p) && k0 <= c0 + (int64_t)p.n * kSB + kSB - 1) block(p, slot + buf * QS * SB);
+    cur = nxt;
+    buf ^= 1;
+  }
+
+  float* const os = reinterpret_cast<float*>(mem);  // [part][key][D], over the slots
+  constexpr int V4 = R * D / 4;                     // 16-byte pieces of the result
+#pragma unroll
+  for (int pass = 0; pass < 2; ++pass) {
+    __syncthreads();
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt) {
+#pragma unroll
+      for (int dt = 0; dt < ND; ++dt)
+        *reinterpret_cast<f32x4*>(os + (qs * R + 32 * kg + 16 * kt + l16) * OP + 16 * dt + 4 * g) =
+            pass ? dv[dt][kt] : dk[dt][kt];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < V4 / NT; ++x) {
+      const int e = (x * NT + tid) * 4, row = e / D, d = e % D;
+      if (kw + row < kv1) {
+        f32x4 acc = *reinterpret_cast<const f32x4*>(os + row * OP + d);
+#pragma unroll
+        for (int y = 1; y < QS; ++y) acc += *reinterpret_cast<const f32x4*>(os + (y * R + row) * OP + d);
+        f32x4* out = reinterpret_cast<f32x4*>((pass ? a.dv : a.dk) + ((b * a.S + kw + row) * a.Hkv + hk) * D + d);
+        const f32x4 old = a.accumulate ? *out : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[v] = pass ? old[v] + acc[v] : __builtin_fmaf(acc[v], a.scale, old[v]);
+        *out = acc;
       }
     }
   }
@@ -822,6 +1207,25 @@ hipError_t launch_bwd_dkdv_bf16(const ChunkArgs& a, hipStream_t stream) {
   if (a.D != 128 && a.D != 64) return hipErrorInvalidValue;
   const int64_t tiles = (a.kv1 - a.kv0 + kKvKeys - 1) / kKvKeys * a.Hkv * a.B;
   if (tiles > 0x7fffffff) return hipErrorInvalidValue;
+  // The split kernels where their workgroups all run at once (one a CU): 32
+  // keys times four parts, then 64 times two (D = 64: 64 times four).  Measured
+  // (us, this kernel -> split, event times): 4 heads, rows [1536, 2048) 32 -> 17
+  // (256 workgroups of 32 keys); 8 heads, rows [1024, 2048) 47 -> 38 (256 of 64);
+  // GQA 16/4, rows [3072, 4096) 127 -> 115; D = 64, GQA 32/8, 2048 rows 145 ->
+  // 113; but 4 heads, rows [7168, 8192) 67 -> 70 (512 of 64), D = 64, 8/2 x
+  // batch 2, rows [3334, 5001) 126 -> 153 (316).  The line is drawn by the whole
+  // chunk's keys, so that launches over parts of [0, c1) give what one launch
+  // gives.
+  const int64_t k64 = (a.c1 + 63) / 64 * a.Hkv * a.B, k32 = (a.c1 + 31) / 32 * a.Hkv * a.B;
+  const int mode = a.D == 128 && k32 <= a.n_cu ? 1 : k64 <= a.n_cu ? 2 : 0;
+  if (mode) {
+    const int r = mode == 2 ? 64 : 32;
+    const dim3 grid((unsigned)((a.kv1 - a.kv0 + r - 1) / r), (unsigned)a.Hkv, (unsigned)a.B);
+    if (a.D == 64) hipLaunchKernelGGL((bwd_dkdv_split_kernel<64, 2, 4>), grid, dim3(512), 0, stream, a);
+    else if (mode == 1) hipLaunchKernelGGL((bwd_dkdv_split_kernel<128, 1, 4>), grid, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL((bwd_dkdv_split_kernel<128, 2, 2>), grid, dim3(256), 0, stream, a);
+    return hipGetLastError();
+  }
   // persistent: as many workgroups as the CUs hold at once
   const int64_t slots = (int64_t)a.n_cu * (a.D == 128 ? dkdv_groups_per_cu<128>() : dkdv_groups_per_cu<64>());
   dim3 grid((unsigned)(tiles < slots ? tiles : slots));
@@ -834,14 +1238,23 @@ hipError_t launch_bwd_dkdv_bf16(const ChunkArgs& a, hipStream_t stream) {
 }
 
 hipError_t launch_bwd_dq_bf16(const ChunkArgs& a, hipStream_t stream) {
+  if (a.D != 128 && a.D != 64) return hipErrorInvalidValue;
   const int64_t s = a.c1 - a.c0;
-  dim3 grid((unsigned)((s + kDqRows - 1) / kDqRows), (unsigned)a.Hq, (unsigned)a.B);
-  if (a.D == 128) {
-    hipLaunchKernelGGL(bwd_dq_bf16_kernel<128>, grid, dim3(256), 0, stream, a);
-  } else if (a.D == 64) {
-    hipLaunchKernelGGL(bwd_dq_bf16_kernel<64>, grid, dim3(256), 0, stream, a);
+  // The split kernel where its workgroups (64 rows; one a CU by LDS at D = 128,
+  // two at D = 64) all run at once.  Measured (us, this kernel -> split, event
+  // times): 4 heads, rows [1536, 2048) 45 -> 29 (32 workgroups); GQA 16/4, rows
+  // [3072, 4096) 80 -> 53 (256); but 32 heads, 1024 rows 30 -> 34 (512); D = 64,
+  // 8 heads x batch 2, rows [3334, 5001) 67 -> 61 (432), 16 heads, rows [6000,
+  // 8000) 102 -> 100 (512).
+  const int64_t groups = (s + 63) / 64 * a.Hq * a.B;
+  if (groups <= (int64_t)a.n_cu * (a.D == 64 ? 2 : 1)) {
+    const dim3 grid((unsigned)((s + 63) / 64), (unsigned)a.Hq, (unsigned)a.B);
+    if (a.D == 128) hipLaunchKernelGGL(bwd_dq_split_kernel<128>, grid, dim3(512), 0, stream, a);
+    else hipLaunchKernelGGL(bwd_dq_split_kernel<64>, grid, dim3(512), 0, stream, a);
   } else {
-    return hipErrorInvalidValue;
+    const dim3 grid((unsigned)((s + kDqRows - 1) / kDqRows), (unsigned)a.Hq, (unsigned)a.B);
+    if (a.D == 128) hipLaunchKernelGGL(bwd_dq_bf16_kernel<128>, grid, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL(bwd_dq_bf16_kernel<64>, grid, dim3(256), 0, stream, a);
   }
   return hipGetLastError();
 }

@@ -40,7 +40,7 @@ constexpr int kSgMFMA = 0x008, kSgVALU = 0x002, kSgDSRead = 0x100, kSgTrans = 0x
 template <int D>
 __global__ __launch_bounds__(256, 2) void fwd_bf16_kernel(ChunkArgs a) {
   constexpr int BR = kFwdBR, BC = kFwdBC;
-  using T = YTile<D>;
+  using T = Tile<D>;
   constexpr int P = T::P;
   constexpr int NK = D / 32;  // k-steps of K Q^T
   constexpr int ND = D / 16;  // 16-wide d tiles of O^T
@@ -374,7 +374,7 @@ __global__ __launch_bounds__(256, 2) void fwd_bf16_kernel(ChunkArgs a) {
 // eight parts is bound by L2 (every 32 rows stream K and V).
 template <int D>
 __global__ __launch_bounds__(512) void fwd_split_kernel(ChunkArgs a) {
-  using T = YTile<D>;
+  using T = Tile<D>;
   constexpr int P = T::P, NK = D / 32, ND = D / 16, RG = 2, KS = 4, R = 32 * RG;
   constexpr int IPW = 32 / T::RPI / RG;  // DMA instructions per wave for each of K and V
   static_assert(IPW >= 1 && IPW * RG * T::RPI == 32, "a sub-block splits over RG waves");

@@ -116,7 +116,7 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_kernel(GemmArgs g) {
   // [64 k-rows][128].
   constexpr int HT = 128 * GBK;  // elements per half tile
   __shared__ __attribute__((aligned(1024))) uint16_t lds[2][4][HT];
-  using T = YTile<TN ? 128 : 64>;
+  using T = Tile<TN ? 128 : 64>;
 
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = w >> 2, wn = w & 3;  // rows 64 wm.. of each A half, cols 32 wn.. of each B half
@@ -297,7 +297,7 @@ __global__ __launch_bounds__(BT == 128 ? 512 : 256, 1) void gemm_small_kernel(Ge
   constexpr int NS = BT == 128 ? 5 : 10;  // 160 KiB
   constexpr int TILE = BT * GBK, DPW = TILE / 512 / NW;  // DMA instructions per wave, operand and k-block
   __shared__ __attribute__((aligned(1024))) uint16_t lds[NS][2][TILE];
-  using T = YTile<TN ? BT : 64>;
+  using T = Tile<TN ? BT : 64>;
 
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = w / WN, wn = w % WN;
@@ -456,12 +456,12 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t stream) {
   // epilogue), in ns as measured.  At 256 CUs: 1000 x 1024 x 4096 takes 69 /
   // 31 / 17 us on 256 / 128 / 64 tiles, 1000 x 4096 x 1024 (GELU) 34 / 17 / 24,
   // 2500 x 9216 x 2304 105 / 130 / 220, 4000 x 2048 x 8192 133 / 140 / 212.
-  struct Tile { int bt; double kb, fixed; };
-  constexpr Tile kTiles[3] = {{256, 1000, 8000}, {128, 500, 6000}, {64, 230, 2500}};
+  struct Option { int bt; double kb, fixed; };
+  constexpr Option kTiles[3] = {{256, 1000, 8000}, {128, 500, 6000}, {64, 230, 2500}};
   const double cus = device_cus(), nkb = (double)((g.K + GBK - 1) / GBK);
   int bt = 0;
   double best = 0;
-  for (const Tile& t : kTiles) {
+  for (const Option& t : kTiles) {
     const double tiles = (double)((g.M + t.bt - 1) / t.bt) * (double)((g.N + t.bt - 1) / t.bt);
     const double ns = __builtin_ceil(tiles / cus) * (nkb * t.kb + t.fixed);
     if (!bt || ns < best) {

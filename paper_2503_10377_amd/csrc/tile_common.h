@@ -2,18 +2,21 @@
 // the bf16 MFMA wrapper, LDS-DMA tile staging, and the swizzled LDS tile
 // layout with its natural and transposed operand reads.
 //
-// MFMA register layout used throughout (v_mfma_f32_32x32x16_bf16, wave64):
-//   A[i][k] : lane l holds row i = l%32 and 8 k-values in "k-slots"
-//   B[k][j] : lane l holds col j = l%32 and 8 k-values in the same k-slots
-//   C[i][j] : lane l holds col j = l%32, rows i = 8*(v/4) + 4*(l/32) + v%4,
-//             v = 0..15
+// MFMA register layout used throughout (v_mfma_f32_16x16x32_bf16, wave64;
+// i = l%16, g = l/16):
+//   A[r][k] : lane l holds row r = i and 8 k-values in "k-slots"
+//   B[k][c] : lane l holds col c = i and 8 k-values in the same k-slots
+//   C[r][c] : lane l holds col c = i, rows r = 4*g + v, v = 0..3
 // Only consistency between the A and B k-slots matters for a product, so
 // each kernel picks the k-slot -> k map that lets it feed one MFMA's C
-// registers straight into the next MFMA: for a 16-wide k-block kb, slot e of
-// lane-half g = l/32 holds k = 16*kb + 8*(e/4) + 4*g + e%4, which is exactly
-// where rows 16*kb.. of a C tile live (v = 8*(kb%2) + e).  A natural-layout
-// operand (k contiguous in memory, e.g. the head dim) uses the plain map
-// k = 16*kk + 8*g + e instead.
+// registers straight into the next MFMA: slot e of group g holds
+// k = 16*(e/4) + 4*g + e%4 of a 32-wide k-block, which is exactly where the
+// rows of two 16-row C tiles live.  A natural-layout operand (k contiguous in
+// memory, e.g. the head dim) uses the plain map k = 32*kk + 8*g + e instead.
+//
+// At the power limit 16x16x32 is the cheaper form of a product: 256 CUs of
+// nothing but MFMAs on N(0,1) operands hold 2.03-2.06 PFLOP/s with it and
+// 1.72-1.81 with 32x32x16.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -24,7 +27,6 @@
 namespace sppo {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
@@ -38,8 +40,8 @@ using IC = std::integral_constant<int, I>;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
-__device__ __forceinline__ f32x16 mfma32(const bf16x8& a, const bf16x8& b, const f32x16& c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+__device__ __forceinline__ f32x4 mfma16(const bf16x8& a, const bf16x8& b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
 __device__ __forceinline__ bf16x8 as_bf16x8(const u32x4& x) { return __builtin_bit_cast(bf16x8, x); }
@@ -191,99 +193,24 @@ __device__ __forceinline__ constexpr int waitcnt_vm(int v) { return (v & 15) | (
 // ---------------------------------------------------------------- LDS tiles
 // A bf16 tile [rows][D] is stored unpadded (row pitch D elements), its
 // 16-byte chunk c of row r at physical chunk c ^ f(r).  The gfx950 LDS has 64
-// four-byte banks (256 bytes); a ds_read_b128 is served 16 lanes at a time
-// and a ds_read_b64_tr_b16 32 lanes at a time.  f spreads both access
-// patterns over all 64 banks:
-//   * natural operand reads: 16 consecutive rows, one chunk each -- f is a
-//     bijection on the low 4 bits of the row (D = 128: a row is one bank
-//     window; D = 64: two rows per window, f bijective per row parity);
-//   * transposed reads: 4 consecutive rows x 4 consecutive chunks per 32
-//     lanes -- the rows land in 4 different 64-byte quarters.
-// Rows are written by LDS-DMA in their physical order (1 KiB per wave
-// instruction), so lane l of an instruction fetches the global chunk that
-// belongs at physical position l.
-template <int D>
-struct XTile {
-  static constexpr int P = D;         // row pitch, elements
-  static constexpr int CG = D / 8;    // 16-byte chunks per row
-  static constexpr int RPI = 512 / D; // rows per LDS-DMA wave instruction
-  static __device__ __forceinline__ int f(int r) {
-    if constexpr (D == 128) {
-      return ((r & 3) << 2) | ((r >> 2) & 3);
-    } else {
-      return (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
-    }
-  }
-  // Natural operand read of k-step kk for rows rb + l%32 (rb % 32 == 0):
-  // element offset (add rb * P).
-  static __device__ __forceinline__ int nat(int lane, int kk) {
-    const int l32 = lane & 31, g = lane >> 5;
-    return l32 * P + 8 * ((2 * kk + g) ^ f(l32));
-  }
-  // Transposed read of rows k0 + {0..7} (hi = 0) or k0 + {8..15} (hi = 1),
-  // columns 32 db..32 db+31 (add k0 * P, k0 % 16 == 0).  Source lane
-  // s = 16q + 4e + a supplies the 8 bytes at row 4(q/2) + e, columns
-  // 16(q%2) + 4a of the 16x32 block; ds_read_b64_tr_b16 hands output lane
-  // 16q + 4a' + b element b of source lanes 16q + 4e + a', e = 0..3.
-  static __device__ __forceinline__ int tr(int lane, int db, int hi) {
-    const int q = lane >> 4, e = (lane >> 2) & 3, a = lane & 3;
-    const int row = 4 * (q >> 1) + e + 8 * hi;
-    const int c = 4 * db + 2 * (q & 1) + (a >> 1);
-    return row * P + 8 * (c ^ f(row)) + 4 * (a & 1);
-  }
-  // Byte offset, relative to the first row of a tile in global memory, of
-  // the chunk lane `lane` fetches in LDS-DMA instruction u of the tile.
-  static __device__ __forceinline__ int dma(int lane, int u, int64_t row_stride) {
-    const int row = RPI * u + lane / CG, p = lane % CG;
-    return (int)((row * row_stride + 8 * (p ^ f(row))) * (int64_t)sizeof(uint16_t));
-  }
-};
-
-__device__ __forceinline__ v4i16 ds_read_tr16(const uint16_t* p) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(p));
-}
-
-// Natural operand: lane l gets row l%32, columns 16 kk + 8 (l/32) + 0..7 of
-// the 32-row block at X (offset from XTile::nat).
-__device__ __forceinline__ bf16x8 ld_nat(const uint16_t* X, int off) {
-  return as_bf16x8(*reinterpret_cast<const u32x4*>(X + off));
-}
-
-// Transposed operand from a natural tile: lane l gets column l%32 of the
-// 32-column block and rows {8(e/4) + 4(l/32) + e%4 : e = 0..7} of the 16-row
-// block, i.e. the permuted k-slot map, so it pairs with an operand taken
-// from C-tile registers.  lo/hi: XTile::tr offsets plus the block's row base.
-__device__ __forceinline__ bf16x8 ld_tr(const uint16_t* X, int lo, int hi) {
-  const v4i16 a = ds_read_tr16(X + lo);
-  const v4i16 b = ds_read_tr16(X + hi);
-  const u32x2 a2 = __builtin_bit_cast(u32x2, a), b2 = __builtin_bit_cast(u32x2, b);
-  return as_bf16x8(u32x4{a2.x, a2.y, b2.x, b2.y});
-}
-
-// ------------------------------------------- 16x16x32 MFMA tiles
-// v_mfma_f32_16x16x32_bf16: lane l (i = l % 16, g = l / 16) holds row / column
-// i and 8 k-values of A / B, and of C column i, rows 4 g + v, v = 0..3.  At
-// the power limit it is the cheaper form of the same product: 256 CUs of
-// nothing but MFMAs on N(0,1) operands hold 2.03-2.06 PFLOP/s with it and
-// 1.72-1.81 with 32x32x16.
-__device__ __forceinline__ f32x4 mfma16(const bf16x8& a, const bf16x8& b, const f32x4& c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-
-// LDS tile [rows][D] for it: as XTile, with the swizzle f chosen for its
-// access patterns:
+// four-byte banks (256 bytes; D = 128: a row is one bank window, D = 64: two
+// rows are).  f spreads every access pattern over all banks:
 //   * natural reads: 16 consecutive rows, chunk 4 kk + g; for D = 64 also of
 //     rows 8 (i / 4) + 4 j + i % 4 (nat_perm).  A ds_read_b128 serves lanes
 //     {0-3, 12-15, 20-27} together, then {4-11, 16-19, 28-31} (and 32 on), so
 //     half of a group's rows come with the neighbouring chunk: f flips chunk
 //     bit 0 with row bit 2 (with row bit 3 instead, every natural read took
 //     twice its cycles);
-//   * transposed reads: 8 consecutive rows x 2 chunks per 32 lanes.
+//   * transposed reads: ds_read_b64_tr_b16 serves 32 lanes at a time, 8
+//     consecutive rows x 2 chunks.
+// Rows are written by LDS-DMA in their physical order (1 KiB per wave
+// instruction), so lane l of an instruction fetches the global chunk that
+// belongs at physical position l.
 template <int D>
-struct YTile {
-  static constexpr int P = D;
-  static constexpr int CG = D / 8;
-  static constexpr int RPI = 512 / D;
+struct Tile {
+  static constexpr int P = D;         // row pitch, elements
+  static constexpr int CG = D / 8;    // 16-byte chunks per row
+  static constexpr int RPI = 512 / D; // rows per LDS-DMA wave instruction
   static __device__ __forceinline__ int f(int r) {
     if constexpr (D == 128) {
       return ((r & 7) << 1) | ((r >> 2) & 1);
@@ -303,18 +230,44 @@ struct YTile {
     const int i = lane & 15, g = lane >> 4, r = rb + 8 * (i >> 2) + 4 * j + (i & 3);
     return r * P + 8 * ((4 * kk + g) ^ f(r));
   }
-  // Transposed operand: lane l gets column 16 blk + i of rows 4 g + 0..3 (add
-  // 16 P for rows 16.. and so on: for D = 128 the swizzle repeats every 8 rows,
-  // for D = 64 row bit 4 swaps column blocks blk and blk ^ 2).
+  // Transposed read of column block blk (16 columns), rows 4 g + 0..3 (add 16 P
+  // for rows 16.. and so on: for D = 128 the swizzle repeats every 8 rows, for
+  // D = 64 row bit 4 swaps column blocks blk and blk ^ 2).  Source lane s = 16g
+  // + 4e + a supplies the 8 bytes at row 4g + e, columns 4a of the block;
+  // ds_read_b64_tr_b16 hands output lane 16g + 4a' + b element b of source
+  // lanes 16g + 4e + a', e = 0..3.
   static __device__ __forceinline__ int tr(int lane, int blk) {
     const int g = lane >> 4, e = (lane >> 2) & 3, a = lane & 3, r = 4 * g + e;
     return r * P + 8 * ((2 * blk + (a >> 1)) ^ f(r)) + 4 * (a & 1);
   }
+  // Byte offset, relative to the first row of a tile in global memory, of
+  // the chunk lane `lane` fetches in LDS-DMA instruction u of the tile.
   static __device__ __forceinline__ int dma(int lane, int u, int64_t row_stride) {
     const int row = RPI * u + lane / CG, p = lane % CG;
     return (int)((row * row_stride + 8 * (p ^ f(row))) * (int64_t)sizeof(uint16_t));
   }
 };
+
+__device__ __forceinline__ v4i16 ds_read_tr16(const uint16_t* p) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(p));
+}
+
+// Natural operand: lane l gets row l%16, columns 32 kk + 8 (l/16) + 0..7 of
+// the 16-row block at X (offset from Tile::nat).
+__device__ __forceinline__ bf16x8 ld_nat(const uint16_t* X, int off) {
+  return as_bf16x8(*reinterpret_cast<const u32x4*>(X + off));
+}
+
+// Transposed operand from a natural tile: lane l gets column l%16 of a
+// 16-column block and rows {16(e/4) + 4(l/16) + e%4 : e = 0..7} of a 32-row
+// block, i.e. the permuted k-slot map, so it pairs with an operand taken from
+// C-tile registers.  lo/hi: Tile::tr offsets of the block's two 16-row halves.
+__device__ __forceinline__ bf16x8 ld_tr(const uint16_t* X, int lo, int hi) {
+  const v4i16 a = ds_read_tr16(X + lo);
+  const v4i16 b = ds_read_tr16(X + hi);
+  const u32x2 a2 = __builtin_bit_cast(u32x2, a), b2 = __builtin_bit_cast(u32x2, b);
+  return as_bf16x8(u32x4{a2.x, a2.y, b2.x, b2.y});
+}
 
 // GELU in its tanh form, x/2 (1 + tanh(u)), u = sqrt(2/pi) (x + 0.044715 x^3),
 // and its derivative; shared by the GEMM epilogues and the recompute kernel
