@@ -14,7 +14,14 @@ bool al16(const void* p) { return p && (reinterpret_cast<uintptr_t>(p) & 15u) ==
 
 sppo_status launched(hipError_t e) { return e == hipSuccess ? SPPO_OK : SPPO_ERR_HIP; }
 
-constexpr int kLnRowsPerBlock = 16;
+// Rows per workgroup of the LayerNorm backward: 16, and from 8192 rows on as
+// many as keep the workgroups at 512 (two a CU), so that their partial sums do
+// not grow with the rows.
+constexpr int kLnRowsPerBlock = 16, kLnMaxBlocks = 512;
+int64_t ln_rows_per_block(int64_t rows) {
+  const int64_t per = (rows + kLnMaxBlocks - 1) / kLnMaxBlocks;
+  return per > kLnRowsPerBlock ? (per + 1) / 2 * 2 : kLnRowsPerBlock;
+}
 
 }  // namespace
 
@@ -68,7 +75,7 @@ sppo_status sppo_layernorm_fwd(int64_t rows, int32_t H, const void* x, int64_t l
 
 size_t sppo_layernorm_bwd_workspace(int64_t rows, int32_t H) {
   if (rows <= 0 || H <= 0) return 0;
-  const int64_t nb = (rows + kLnRowsPerBlock - 1) / kLnRowsPerBlock;
+  const int64_t per = ln_rows_per_block(rows), nb = (rows + per - 1) / per;
   return (size_t)nb * 2 * (size_t)H * sizeof(float);
 }
 
@@ -93,7 +100,7 @@ sppo_status sppo_layernorm_bwd(int64_t rows, int32_t H, const void* x, int64_t l
   l.dy = static_cast<const uint16_t*>(dy); l.lddy = lddy;
   l.dres = static_cast<const uint16_t*>(dres); l.lddres = lddres;
   l.dgamma = dgamma; l.dbeta = dbeta; l.part = workspace;
-  l.rows_per_block = kLnRowsPerBlock;
+  l.rows_per_block = (int)ln_rows_per_block(rows);
   l.accumulate = accumulate != 0;
   return launched(sppo::launch_ln_bwd(l, static_cast<hipStream_t>(stream)));
 }

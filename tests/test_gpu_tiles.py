@@ -135,3 +135,49 @@ def test_bf16_evicting_walk_equals_resident_by_kernel_choice(Hq, Hkv, D, offsets
            for o in ("qkvol", "qkvol_evict")]
     for n in ("o", "lse", "dq", "dk", "dv"):
         assert np.array_equal(res[0][n], res[1][n]), n
+
+
+# One wave per row up to 1024 columns, then 256 / 384 / 512 threads; the backward's
+# workgroups take 16 rows in pairs, and from 8192 rows on more.
+@pytest.mark.parametrize("rows,H", [(3, 8), (37, 512), (34, 520), (19, 1024), (18, 1032), (17, 2048), (5, 4104),
+                                    (16, 6152), (8192, 64), (8195, 136), (9000, 1040)])
+def test_layernorm_teams(rows, H):
+    announce(f"layernorm teams rows={rows} H={H}")
+    g = torch.Generator().manual_seed(rows * 7 + H)
+    x, dy, dres = [(torch.randn(rows, H, generator=g) + b).to(torch.bfloat16) for b in (0.5, 0.0, 0.0)]
+    gamma, beta = 1 + 0.1 * torch.randn(H, generator=g), 0.1 * torch.randn(H, generator=g)
+    y, dx = torch.empty(rows, H, device="cuda", dtype=torch.bfloat16), dres.cuda()  # dx in place of dres
+    mean, rstd = torch.empty(rows, device="cuda"), torch.empty(rows, device="cuda")
+    dg, db = torch.full((H,), 2.0, device="cuda"), torch.full((H,), -1.0, device="cuda")
+    wsb = L.sppo_layernorm_bwd_workspace(rows, H)
+    ws = torch.full((wsb // 4 + 2,), float("nan"), device="cuda")[1:-1]  # a float's alignment, a word free on each side
+    xd, gd = x.cuda(), gamma.cuda()
+    L.sppo_layernorm_fwd(rows, H, xd, H, gd, beta.cuda(), 1e-5, y, H, mean, rstd)
+    L.sppo_layernorm_bwd(rows, H, xd, H, gd, mean, rstd, dy.cuda(), H, dx, H, dx, H, dg, db, ws, wsb, 1)
+    torch.cuda.synchronize()
+    assert ws._base[0].isnan() and ws._base[-1].isnan(), "wrote outside the workspace"
+    x, dy, dres, gamma, beta = [t.double() for t in (x, dy, dres, gamma, beta)]
+    mu = x.mean(1, keepdim=True)
+    r = (x.var(1, unbiased=False, keepdim=True) + 1e-5).rsqrt()
+    xh = (x - mu) * r
+    gg = dy * gamma
+    wdx = dres + r * (gg - gg.mean(1, keepdim=True) - xh * (gg * xh).mean(1, keepdim=True))
+    # bf16 results: half an ulp (2^-9), and 64 fp32 roundings of terms up to the row's largest.
+    for got, want in ((y, xh * gamma + beta), (dx, wdx)):
+        lim = want.abs() * 2.0**-8 + 64 * 2.0**-24 * want.abs().amax(1, keepdim=True) * (1 + r)
+        assert ((got.cpu().double() - want).abs() <= lim).all()
+    # fp32 sums over rows: at most 160 additions in any term's chain, and 32 roundings in the term.
+    for got, t, base in ((dg, dy * xh, 2.0), (db, dy, -1.0)):
+        lim = 192 * 2.0**-24 * (t.abs().sum(0) + abs(base))
+        assert ((got.cpu().double() - base - t.sum(0)).abs() <= lim).all()
+
+
+# 16 bytes per lane where rows and columns come in eights and the buffers are aligned.
+@pytest.mark.parametrize("R,C,off", [(8, 8, 0), (64, 64, 0), (72, 264, 0), (200, 56, 0), (64, 64, 1), (64, 72, 4)])
+def test_transpose_wide(R, C, off):
+    announce(f"transpose {R}x{C} offset {off}")
+    x = torch.randn(R * C + off).to(torch.bfloat16).cuda()[off:]
+    y = torch.full((R * C + off + 8,), 3.0, device="cuda", dtype=torch.bfloat16)
+    L.sppo_transpose_bf16(x, y[off:], R, C)
+    torch.cuda.synchronize()
+    assert torch.equal(y[off:off + R * C].view(C, R), x.view(R, C).t()) and (y[off + R * C:] == 3.0).all()
