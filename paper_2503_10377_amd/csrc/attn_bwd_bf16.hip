@@ -781,29 +781,33 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_bf16_kernel(ChunkArgs a) {
   }
 }
 
-// dQ for grids that leave compute units idle: a workgroup is 8 waves, two groups
-// of 32 query rows of one head times four parts of the keys (part ks has the
-// 32-key sub-blocks u = ks, ks + 4, ...); the parts are added through LDS in
-// part order.  A sub-block's part depends on its position in the sequence
-// alone, so a row's result does not depend on the chunking.
-template <int D>
-__global__ __launch_bounds__(512) void bwd_dq_split_kernel(ChunkArgs a) {
+// dQ for grids that leave compute units idle: a workgroup is RG groups of 32
+// query rows of one head times four parts of the keys (part ks has the 32-key
+// sub-blocks u = ks, ks + 4, ...), a wave each; the parts are added through LDS
+// in part order.  A sub-block's part depends on its position in the sequence
+// alone, so a row's result depends neither on the chunking nor on RG.
+// bwd_dq_split is one workgroup's work: position gp of a grid nx tiles wide, in
+// the kDqSplitBytes bytes of LDS at mem.
+constexpr int kDqParts = 4;
+template <int D, int RG>
+constexpr int kDqSplitBytes = 2 * kDqParts * 2 * kSB * Tile<D>::P * 2 > kDqParts * 32 * RG * (D + 4) * 4
+                                  ? 2 * kDqParts * 2 * kSB * Tile<D>::P * 2
+                                  : kDqParts * 32 * RG * (D + 4) * 4;
+template <int D, int RG>
+__device__ __forceinline__ void bwd_dq_split(const ChunkArgs& a, const GridPos gp, int nx, unsigned char* mem) {
   using T = Tile<D>;
-  constexpr int P = T::P, NK = D / 32, ND = D / 16, RG = 2, KS = 4, R = 32 * RG;
+  constexpr int P = T::P, NK = D / 32, ND = D / 16, KS = kDqParts, R = 32 * RG;
   constexpr int IPW = 32 / T::RPI / RG;  // DMA instructions per wave for each of K and V
   constexpr int SB = 2 * kSB * P;        // elements of a sub-block's K and V
   constexpr int OP = D + 4;              // row pitch of the partial dQ's, floats
-  constexpr int kBytes = 2 * KS * SB * 2 > KS * R * OP * 4 ? 2 * KS * SB * 2 : KS * R * OP * 4;
-  __shared__ __attribute__((aligned(1024))) unsigned char mem[kBytes];
 
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g = lane >> 4, rg = w % RG, ks = w / RG;
-  const GridPos gp = xcd_grouped();
   const int h = gp.y;
   const int64_t b = gp.z;
   const int hk = h / (a.Hq / a.Hkv);
   const int64_t c0 = a.c0, c1 = a.c1, s = c1 - c0;
-  const int64_t q0 = c0 + (int64_t)(gridDim.x - 1 - gp.x) * R;
+  const int64_t q0 = c0 + (int64_t)(nx - 1 - gp.x) * R;
   const int64_t qw = q0 + 32 * rg, r = qw + l16;  // this lane's rows: r and r + 16
   const int64_t kend = q0 + R < c1 ? q0 + R : c1;
   const int nsub = (int)((kend + kSB - 1) / kSB), nstep = (nsub + KS - 1) / KS;
@@ -929,7 +933,7 @@ __global__ __launch_bounds__(512) void bwd_dq_split_kernel(ChunkArgs a) {
       *reinterpret_cast<f32x4*>(os + (ks * R + 32 * rg + 16 * qt + l16) * OP + 16 * dt + 4 * g) = dq[dt][qt];
   }
   __syncthreads();
-  constexpr int TPR = 512 / R, EPT = D / TPR;  // threads per row, elements per thread
+  constexpr int TPR = 64 * RG * KS / R, EPT = D / TPR;  // threads per row, elements per thread
   const int row = tid / TPR, d0 = (tid % TPR) * EPT;
   if (q0 + row >= c1) return;
   uint16_t* qrow = static_cast<uint16_t*>(a.dq) + ((b * s + (q0 + row - c0)) * a.Hq + h) * D + d0;
@@ -942,6 +946,11 @@ __global__ __launch_bounds__(512) void bwd_dq_split_kernel(ChunkArgs a) {
         pack_bf16x4(acc[0] * a.scale, acc[1] * a.scale, acc[2] * a.scale, acc[3] * a.scale);
   }
 }
+template <int D>
+__global__ __launch_bounds__(512) void bwd_dq_split_kernel(ChunkArgs a) {
+  __shared__ __attribute__((aligned(1024))) unsigned char mem[kDqSplitBytes<D, 2>];
+  bwd_dq_split<D, 2>(a, xcd_grouped(), gridDim.x, mem);
+}
 
 // dK/dV for grids that leave compute units idle: KG groups of 32 keys of one KV
 // head times QS parts of the chunk's query sub-blocks (32 rows; sub-block n of
@@ -951,19 +960,20 @@ __global__ __launch_bounds__(512) void bwd_dq_split_kernel(ChunkArgs a) {
 // the range of keys a launch covers.  D = 128: 4 waves, one per SIMD by their
 // accumulators and K/V fragments; D = 64: 8.
 template <int D, int KG, int QS>
-__global__ __launch_bounds__(64 * KG * QS) void bwd_dkdv_split_kernel(ChunkArgs a) {
+constexpr int kDkdvSplitBytes = 2 * QS * 2 * kSB * Tile<D>::P * 2 > QS * 32 * KG * (D + 4) * 4
+                                    ? 2 * QS * 2 * kSB * Tile<D>::P * 2
+                                    : QS * 32 * KG * (D + 4) * 4;
+template <int D, int KG, int QS>
+__device__ __forceinline__ void bwd_dkdv_split(const ChunkArgs& a, const GridPos gp, unsigned char* mem) {
   using T = Tile<D>;
   constexpr int P = T::P, NK = D / 32, ND = D / 16, NT = 64 * KG * QS, R = 32 * KG;
   constexpr int IPW = 32 / T::RPI / KG;  // DMA instructions per wave for each of Q and dO
   static_assert(IPW >= 1 && IPW * KG * T::RPI == 32, "a sub-block splits over KG waves");
   constexpr int SB = 2 * kSB * P;  // elements of a sub-block's Q and dO
   constexpr int OP = D + 4;        // row pitch of the partial sums, floats
-  constexpr int kBytes = 2 * QS * SB * 2 > QS * R * OP * 4 ? 2 * QS * SB * 2 : QS * R * OP * 4;
-  __shared__ __attribute__((aligned(1024))) unsigned char mem[kBytes];
 
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g = lane >> 4, kg = w % KG, qs = w / KG;
-  const GridPos gp = xcd_grouped();
   const int hk = gp.y, G = a.Hq / a.Hkv;
   const int64_t b = gp.z;
   const int64_t c0 = a.c0, c1 = a.c1, s = c1 - c0, kv1 = a.kv1;
@@ -1169,6 +1179,31 @@ __global__ __launch_bounds__(64 * KG * QS) void bwd_dkdv_split_kernel(ChunkArgs 
     }
   }
 }
+template <int D, int KG, int QS>
+__global__ __launch_bounds__(64 * KG * QS) void bwd_dkdv_split_kernel(ChunkArgs a) {
+  __shared__ __attribute__((aligned(1024))) unsigned char mem[kDkdvSplitBytes<D, KG, QS>];
+  bwd_dkdv_split<D, KG, QS>(a, xcd_grouped(), mem);
+}
+
+// Both of a chunk's split kernels as one launch: neither needs the other's
+// results, and one after the other each leaves most of the card idle.  The
+// kind with the longer workgroups comes first (dq_first).
+struct PairGrid {
+  int dq_first, ndq, dqx, ndkdv, dkdvx;  // workgroups of each kind, and tiles in x
+};
+template <int D, int KG, int QS>
+__global__ __launch_bounds__(64 * KG * QS) void bwd_pair_kernel(ChunkArgs a, PairGrid p) {
+  constexpr int RG = KG * QS / kDqParts, nq = kDqSplitBytes<D, RG>, nk = kDkdvSplitBytes<D, KG, QS>;
+  static_assert(RG * kDqParts == KG * QS, "both kinds have the same waves");
+  __shared__ __attribute__((aligned(1024))) unsigned char mem[nq > nk ? nq : nk];
+  const int n = blockIdx.x, lead = p.dq_first ? p.ndq : p.ndkdv;
+  const bool dq = p.dq_first ? n < lead : n >= lead;
+  const int m = n < lead ? n : n - lead;
+  if (dq)
+    bwd_dq_split<D, RG>(a, xcd_grouped(m, p.dqx, a.Hq, (uint32_t)a.B), p.dqx, mem);
+  else
+    bwd_dkdv_split<D, KG, QS>(a, xcd_grouped(m, p.dkdvx, a.Hkv, (uint32_t)a.B), mem);
+}
 
 }  // namespace
 
@@ -1202,22 +1237,28 @@ int dkdv_groups_per_cu() {
   return n;
 }
 
+// Which dK/dV kernel: 0 the persistent one, 1 split with 32 keys a workgroup, 2
+// split with 64.
+// The split kernels where their workgroups all run at once (one a CU): 32
+// keys times four parts, then 64 times two (D = 64: 64 times four).  Measured
+// (us, this kernel -> split, event times): 4 heads, rows [1536, 2048) 32 -> 17
+// (256 workgroups of 32 keys); 8 heads, rows [1024, 2048) 47 -> 38 (256 of 64);
+// GQA 16/4, rows [3072, 4096) 127 -> 115; D = 64, GQA 32/8, 2048 rows 145 ->
+// 113; but 4 heads, rows [7168, 8192) 67 -> 70 (512 of 64), D = 64, 8/2 x
+// batch 2, rows [3334, 5001) 126 -> 153 (316).  The line is drawn by the whole
+// chunk's keys, so that launches over parts of [0, c1) give what one launch
+// gives.
+static int dkdv_split_mode(const ChunkArgs& a) {
+  const int64_t k64 = (a.c1 + 63) / 64 * a.Hkv * a.B, k32 = (a.c1 + 31) / 32 * a.Hkv * a.B;
+  return a.D == 128 && k32 <= a.n_cu ? 1 : k64 <= a.n_cu ? 2 : 0;
+}
+
 hipError_t launch_bwd_dkdv_bf16(const ChunkArgs& a, hipStream_t stream) {
   if (a.kv0 < 0 || a.kv1 > a.c1 || a.kv0 >= a.kv1 || !a.tiles || a.n_cu < 1) return hipErrorInvalidValue;
   if (a.D != 128 && a.D != 64) return hipErrorInvalidValue;
   const int64_t tiles = (a.kv1 - a.kv0 + kKvKeys - 1) / kKvKeys * a.Hkv * a.B;
   if (tiles > 0x7fffffff) return hipErrorInvalidValue;
-  // The split kernels where their workgroups all run at once (one a CU): 32
-  // keys times four parts, then 64 times two (D = 64: 64 times four).  Measured
-  // (us, this kernel -> split, event times): 4 heads, rows [1536, 2048) 32 -> 17
-  // (256 workgroups of 32 keys); 8 heads, rows [1024, 2048) 47 -> 38 (256 of 64);
-  // GQA 16/4, rows [3072, 4096) 127 -> 115; D = 64, GQA 32/8, 2048 rows 145 ->
-  // 113; but 4 heads, rows [7168, 8192) 67 -> 70 (512 of 64), D = 64, 8/2 x
-  // batch 2, rows [3334, 5001) 126 -> 153 (316).  The line is drawn by the whole
-  // chunk's keys, so that launches over parts of [0, c1) give what one launch
-  // gives.
-  const int64_t k64 = (a.c1 + 63) / 64 * a.Hkv * a.B, k32 = (a.c1 + 31) / 32 * a.Hkv * a.B;
-  const int mode = a.D == 128 && k32 <= a.n_cu ? 1 : k64 <= a.n_cu ? 2 : 0;
+  const int mode = dkdv_split_mode(a);
   if (mode) {
     const int r = mode == 2 ? 64 : 32;
     const dim3 grid((unsigned)((a.kv1 - a.kv0 + r - 1) / r), (unsigned)a.Hkv, (unsigned)a.B);
@@ -1237,17 +1278,20 @@ hipError_t launch_bwd_dkdv_bf16(const ChunkArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// The split kernel where its workgroups (64 rows; one a CU by LDS at D = 128,
+// two at D = 64) all run at once.  Measured (us, this kernel -> split, event
+// times): 4 heads, rows [1536, 2048) 45 -> 29 (32 workgroups); GQA 16/4, rows
+// [3072, 4096) 80 -> 53 (256); but 32 heads, 1024 rows 30 -> 34 (512); D = 64,
+// 8 heads x batch 2, rows [3334, 5001) 67 -> 61 (432), 16 heads, rows [6000,
+// 8000) 102 -> 100 (512).
+static bool dq_split(const ChunkArgs& a) {
+  return (a.c1 - a.c0 + 63) / 64 * a.Hq * a.B <= (int64_t)a.n_cu * (a.D == 64 ? 2 : 1);
+}
+
 hipError_t launch_bwd_dq_bf16(const ChunkArgs& a, hipStream_t stream) {
   if (a.D != 128 && a.D != 64) return hipErrorInvalidValue;
   const int64_t s = a.c1 - a.c0;
-  // The split kernel where its workgroups (64 rows; one a CU by LDS at D = 128,
-  // two at D = 64) all run at once.  Measured (us, this kernel -> split, event
-  // times): 4 heads, rows [1536, 2048) 45 -> 29 (32 workgroups); GQA 16/4, rows
-  // [3072, 4096) 80 -> 53 (256); but 32 heads, 1024 rows 30 -> 34 (512); D = 64,
-  // 8 heads x batch 2, rows [3334, 5001) 67 -> 61 (432), 16 heads, rows [6000,
-  // 8000) 102 -> 100 (512).
-  const int64_t groups = (s + 63) / 64 * a.Hq * a.B;
-  if (groups <= (int64_t)a.n_cu * (a.D == 64 ? 2 : 1)) {
+  if (dq_split(a)) {
     const dim3 grid((unsigned)((s + 63) / 64), (unsigned)a.Hq, (unsigned)a.B);
     if (a.D == 128) hipLaunchKernelGGL(bwd_dq_split_kernel<128>, grid, dim3(512), 0, stream, a);
     else hipLaunchKernelGGL(bwd_dq_split_kernel<64>, grid, dim3(512), 0, stream, a);
@@ -1256,6 +1300,42 @@ hipError_t launch_bwd_dq_bf16(const ChunkArgs& a, hipStream_t stream) {
     if (a.D == 128) hipLaunchKernelGGL(bwd_dq_bf16_kernel<128>, grid, dim3(256), 0, stream, a);
     else hipLaunchKernelGGL(bwd_dq_bf16_kernel<64>, grid, dim3(256), 0, stream, a);
   }
+  return hipGetLastError();
+}
+
+// The workgroups of both kinds of a chunk's split backward as one launch, if
+// both take the split kernels, they are at most two to a place on the card, and
+// dQ overwrites nothing the dK/dV reads.  Measured (us, pre + dK/dV + dQ, one
+// after the other -> pair): 4 heads, rows [0, 512) 27.9 -> 16.5, [1536, 2048)
+// 43.3 -> 28.6 (320 workgroups on 256 CUs); 8 heads, rows [1024, 2048) 64.1 ->
+// 53.9 (512); D = 64, 8/2 x batch 2, rows [1667, 3334) 138 -> 115; but GQA 16/4,
+// rows [3072, 4096) 166 -> 183 and 8/2, rows [2048, 4096) 182 -> 192 (768).
+static bool pair_grid(const ChunkArgs& a, PairGrid* p) {
+  const int mode = dkdv_split_mode(a);
+  if ((a.D != 128 && a.D != 64) || !mode || !dq_split(a)) return false;
+  const int64_t s = a.c1 - a.c0, rows = a.D == 64 ? 64 : 32, keys = mode == 2 ? 64 : 32;
+  const int64_t dqx = (s + rows - 1) / rows, dkdvx = (a.kv1 - a.kv0 + keys - 1) / keys;
+  const int64_t ndq = dqx * a.Hq * a.B, ndkdv = dkdvx * a.Hkv * a.B;
+  if (ndq + ndkdv > (int64_t)a.n_cu * (a.D == 64 ? 4 : 2)) return false;
+  if (dq_overwrites_inputs(a, 2)) return false;
+  const int64_t parts = a.D == 128 && mode == 2 ? 2 : 4;
+  const int dq_first = a.c1 / kDqParts >= a.Hq / a.Hkv * s / parts;
+  *p = PairGrid{dq_first, (int)ndq, (int)dqx, (int)ndkdv, (int)dkdvx};
+  return true;
+}
+
+bool bwd_pair_bf16(const ChunkArgs& a) {
+  PairGrid p;
+  return pair_grid(a, &p);
+}
+
+hipError_t launch_bwd_pair_bf16(const ChunkArgs& a, hipStream_t stream) {
+  PairGrid p;
+  if (a.kv0 < 0 || a.kv1 > a.c1 || a.kv0 >= a.kv1 || !pair_grid(a, &p)) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)(p.ndq + p.ndkdv));
+  if (a.D == 64) hipLaunchKernelGGL((bwd_pair_kernel<64, 2, 4>), grid, dim3(512), 0, stream, a, p);
+  else if (dkdv_split_mode(a) == 1) hipLaunchKernelGGL((bwd_pair_kernel<128, 1, 4>), grid, dim3(256), 0, stream, a, p);
+  else hipLaunchKernelGGL((bwd_pair_kernel<128, 2, 2>), grid, dim3(256), 0, stream, a, p);
   return hipGetLastError();
 }
 

@@ -291,16 +291,15 @@ __global__ __launch_bounds__(256) void pre_f32_kernel(ChunkArgs a) {
   }
 }
 
+// One workgroup's dQ tile: tile x of nx, query head h, batch entry b.
 template <int D>
-__global__ __launch_bounds__(512) void dq_f32_kernel(ChunkArgs a) {
+__device__ __forceinline__ void dq_tile(const ChunkArgs& a, int x, int nx, int h, int64_t b,
+                                        float (*Qs)[kB * (D + 4)]) {
   constexpr int W = 8;
-  __shared__ __attribute__((aligned(16))) float Qs[W][kB * (D + 4)];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
-  const int h = blockIdx.y;
-  const int64_t b = blockIdx.z;
   const int hk = h / (a.Hq / a.Hkv);
   const int64_t c0 = a.c0, c1 = a.c1, s = c1 - c0;
-  const int64_t q0 = c0 + (int64_t)(gridDim.x - 1 - blockIdx.x) * kB;
+  const int64_t q0 = c0 + (int64_t)(nx - 1 - x) * kB;
   const int64_t r = q0 + i, rc = r < c1 ? r : c1 - 1;
   const int64_t kend = (q0 + kB < c1) ? q0 + kB : c1;
   const int64_t off = ((b * s + (rc - c0)) * a.Hq + h) * D;
@@ -352,22 +351,28 @@ __global__ __launch_bounds__(512) void dq_f32_kernel(ChunkArgs a) {
   for (int d = d0; d < D; d += TPR) {
     float acc = Qs[0][row * (D + 4) + d];
 #pragma unroll
-    for (int x = 1; x < W; ++x) acc += Qs[x][row * (D + 4) + d];
+    for (int y = 1; y < W; ++y) acc += Qs[y][row * (D + 4) + d];
     out[d] = acc * a.scale;
   }
+}
+template <int D>
+__global__ __launch_bounds__(512) void dq_f32_kernel(ChunkArgs a) {
+  __shared__ __attribute__((aligned(16))) float Qs[8][kB * (D + 4)];
+  dq_tile<D>(a, blockIdx.x, gridDim.x, blockIdx.y, blockIdx.z, Qs);
 }
 
 // Waves: 8 for D = 64; 4 for D = 128, whose fragments, accumulators and
 // operands (about 260 registers) leave room for one wave per SIMD.
 template <int D>
-__global__ __launch_bounds__(D == 64 ? 512 : 256) void dkdv_f32_kernel(ChunkArgs a) {
-  constexpr int W = D == 64 ? 8 : 4, T = 64 * W;
-  __shared__ __attribute__((aligned(16))) float Ks[W][kB * (D + 4)];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4, hk = blockIdx.y;
-  const int64_t b = blockIdx.z;
+constexpr int kDkdvWaves = D == 64 ? 8 : 4;
+// One workgroup's dK/dV tile: tile x from kv0, KV head hk, batch entry b.
+template <int D>
+__device__ __forceinline__ void dkdv_tile(const ChunkArgs& a, int x, int hk, int64_t b, float (*Ks)[kB * (D + 4)]) {
+  constexpr int W = kDkdvWaves<D>, T = 64 * W;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
   const int G = a.Hq / a.Hkv;
   const int64_t c0 = a.c0, c1 = a.c1, s = c1 - c0;
-  const int64_t k0 = a.kv0 + (int64_t)blockIdx.x * kB;
+  const int64_t k0 = a.kv0 + (int64_t)x * kB;
   const int64_t j = k0 + i, jc = j < a.kv1 ? j : a.kv1 - 1;
   const int64_t kvoff = ((b * a.S + jc) * a.Hkv + hk) * D;
   f32x4 kx[D / 16], vx[D / 16], dk[D / 64][4], dv[D / 64][4];
@@ -449,6 +454,27 @@ __global__ __launch_bounds__(D == 64 ? 512 : 256) void dkdv_f32_kernel(ChunkArgs
     }
   }
 }
+template <int D>
+__global__ __launch_bounds__(64 * kDkdvWaves<D>) void dkdv_f32_kernel(ChunkArgs a) {
+  __shared__ __attribute__((aligned(16))) float Ks[kDkdvWaves<D>][kB * (D + 4)];
+  dkdv_tile<D>(a, blockIdx.x, blockIdx.y, blockIdx.z, Ks);
+}
+
+// Both of a chunk's gradient kernels as one launch (D = 64, where their
+// workgroups are alike): neither needs the other's results, and one after the
+// other each leaves the card idle for a small grid or at its end.  dQ tiles
+// first; dqx and kx tiles in x.
+__global__ __launch_bounds__(512) void pair_f32_kernel(ChunkArgs a, int dqx, int kx) {
+  constexpr int D = 64;
+  __shared__ __attribute__((aligned(16))) float mem[8][kB * (D + 4)];
+  const int ndq = dqx * a.Hq * (int)a.B, n = blockIdx.x;
+  if (n < ndq) {
+    dq_tile<D>(a, n % dqx, dqx, n / dqx % a.Hq, n / (dqx * a.Hq), mem);
+  } else {
+    const int m = n - ndq;
+    dkdv_tile<D>(a, m % kx, m / kx % a.Hkv, m / (kx * a.Hkv), mem);
+  }
+}
 
 }  // namespace
 
@@ -502,6 +528,24 @@ hipError_t launch_bwd_dq_f32(const ChunkArgs& a, hipStream_t stream) {
   } else {
     return hipErrorInvalidValue;
   }
+  return hipGetLastError();
+}
+
+// At any size where the workgroups are alike (us, pre + dK/dV + dQ, one after
+// the other -> pair: 4 heads, rows [0, 256) 23.9 -> 15.2, [768, 1024) 38.2 ->
+// 26.6; 8 heads, rows [1000, 2000) 196 -> 189; 16 heads, 2048 rows 542 -> 543).
+bool bwd_pair_f32(const ChunkArgs& a) {
+  if (a.D != 64) return false;
+  const int64_t s = a.c1 - a.c0;
+  const int64_t groups = (s + kB - 1) / kB * a.Hq * a.B + (a.kv1 - a.kv0 + kB - 1) / kB * a.Hkv * a.B;
+  return groups <= 0x7fffffff && !dq_overwrites_inputs(a, 4);
+}
+
+hipError_t launch_bwd_pair_f32(const ChunkArgs& a, hipStream_t stream) {
+  if (a.kv0 < 0 || a.kv1 > a.c1 || a.kv0 >= a.kv1 || !bwd_pair_f32(a)) return hipErrorInvalidValue;
+  const int64_t s = a.c1 - a.c0, dqx = (s + kB - 1) / kB, kx = (a.kv1 - a.kv0 + kB - 1) / kB;
+  const dim3 grid((unsigned)(dqx * a.Hq * a.B + kx * a.Hkv * a.B));
+  hipLaunchKernelGGL(pair_f32_kernel, grid, dim3(512), 0, stream, a, (int)dqx, (int)kx);
   return hipGetLastError();
 }
 

@@ -139,8 +139,12 @@ extern "C" sppo_status sppo_attn_bwd_chunk_noalloc(int64_t batch, int64_t seq_le
   hipStream_t sm = static_cast<hipStream_t>(stream);
   const bool bf16 = dtype == SPPO_BF16;
   hipError_t e = bf16 ? sppo::launch_bwd_pre_bf16(a, sm) : sppo::launch_bwd_pre_f32(a, sm);
-  if (e == hipSuccess) e = bf16 ? sppo::launch_bwd_dkdv_bf16(a, sm) : sppo::launch_bwd_dkdv_f32(a, sm);
-  if (e == hipSuccess) e = bf16 ? sppo::launch_bwd_dq_bf16(a, sm) : sppo::launch_bwd_dq_f32(a, sm);
+  if (bf16 ? sppo::bwd_pair_bf16(a) : sppo::bwd_pair_f32(a)) {
+    if (e == hipSuccess) e = bf16 ? sppo::launch_bwd_pair_bf16(a, sm) : sppo::launch_bwd_pair_f32(a, sm);
+  } else {
+    if (e == hipSuccess) e = bf16 ? sppo::launch_bwd_dkdv_bf16(a, sm) : sppo::launch_bwd_dkdv_f32(a, sm);
+    if (e == hipSuccess) e = bf16 ? sppo::launch_bwd_dq_bf16(a, sm) : sppo::launch_bwd_dq_f32(a, sm);
+  }
   if (e != hipSuccess) return fail(SPPO_ERR_HIP, std::string("backward kernel launch: ") + hipGetErrorString(e));
   return SPPO_OK;
 }

@@ -685,7 +685,11 @@ sppo_status sppo_attn_bwd_chunk(sppo_ctx* ctx, int32_t i, const void* q_i, const
   hipError_t e = timed_launch(ctx, SPPO_KERNEL_BWD_PRE, i, s, [&] {
     return bf16 ? sppo::launch_bwd_pre_bf16(a, s) : sppo::launch_bwd_pre_f32(a, s);
   });
-  if (e == hipSuccess && !pieces) {
+  // One launch for both where that is the faster (the same results); kernel
+  // timing times them one by one.
+  const bool pair = !pieces && !ctx->ktiming && (bf16 ? sppo::bwd_pair_bf16(a) : sppo::bwd_pair_f32(a));
+  if (e == hipSuccess && pair) e = bf16 ? sppo::launch_bwd_pair_bf16(a, s) : sppo::launch_bwd_pair_f32(a, s);
+  if (e == hipSuccess && !pieces && !pair) {
     e = timed_launch(ctx, SPPO_KERNEL_BWD_DKDV, i, s, [&] {
       return bf16 ? sppo::launch_bwd_dkdv_bf16(a, s) : sppo::launch_bwd_dkdv_f32(a, s);
     });
@@ -702,7 +706,7 @@ sppo_status sppo_attn_bwd_chunk(sppo_ctx* ctx, int32_t i, const void* q_i, const
       return bf16 ? sppo::launch_bwd_dkdv_bf16(aj, s) : sppo::launch_bwd_dkdv_f32(aj, s);
     });
   }
-  if (e == hipSuccess) {
+  if (e == hipSuccess && !pair) {
     e = timed_launch(ctx, SPPO_KERNEL_BWD_DQ, i, s, [&] {
       return bf16 ? sppo::launch_bwd_dq_bf16(a, s) : sppo::launch_bwd_dq_f32(a, s);
     });

@@ -48,15 +48,34 @@ constexpr int kTileQueueInts = 16;
 // Each launcher enqueues one kernel on `stream` and returns the launch
 // status.  The backward of a chunk is pre (Delta), then dkdv (one launch for
 // key rows [kv0, kv1); several launches over disjoint ranges give the same
-// result), then dq.
+// result), then dq; or pre, then pair (all of dkdv and dq in one launch, the
+// same results) where bwd_pair says so: small grids that one launch of each
+// leaves mostly idle.
 hipError_t launch_fwd_bf16(const ChunkArgs& a, hipStream_t stream);
 hipError_t launch_bwd_pre_bf16(const ChunkArgs& a, hipStream_t stream);
 hipError_t launch_bwd_dkdv_bf16(const ChunkArgs& a, hipStream_t stream);
 hipError_t launch_bwd_dq_bf16(const ChunkArgs& a, hipStream_t stream);
+bool bwd_pair_bf16(const ChunkArgs& a);
+hipError_t launch_bwd_pair_bf16(const ChunkArgs& a, hipStream_t stream);
 hipError_t launch_fwd_f32(const ChunkArgs& a, hipStream_t stream);
 hipError_t launch_bwd_pre_f32(const ChunkArgs& a, hipStream_t stream);
 hipError_t launch_bwd_dkdv_f32(const ChunkArgs& a, hipStream_t stream);
 hipError_t launch_bwd_dq_f32(const ChunkArgs& a, hipStream_t stream);
+bool bwd_pair_f32(const ChunkArgs& a);
+hipError_t launch_bwd_pair_f32(const ChunkArgs& a, hipStream_t stream);
+
+// Whether dQ shares memory with what the dK/dV kernels read (elements of elt
+// bytes): a caller may let dQ replace Q or dO, which holds only while dQ runs
+// after dK/dV.
+inline bool dq_overwrites_inputs(const ChunkArgs& a, int64_t elt) {
+  const int64_t nq = a.B * (a.c1 - a.c0) * a.Hq * a.D * elt, nk = a.B * a.S * a.Hkv * a.D * elt;
+  const uintptr_t dq = reinterpret_cast<uintptr_t>(a.dq);
+  const auto shares = [&](const void* p, int64_t n) {
+    const uintptr_t lo = reinterpret_cast<uintptr_t>(p);
+    return lo < dq + nq && dq < lo + n;
+  };
+  return shares(a.q, nq) || shares(a.dout, nq) || shares(a.k, nk) || shares(a.v, nk);
+}
 
 // Rounding of finished dK/dV rows: out_k/out_v rows [row0, row0 + rows) of
 // every batch entry = dk/dv rows (fp32 [B, S, W], W = Hkv * D, W % 8 == 0),

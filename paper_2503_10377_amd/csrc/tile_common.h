@@ -145,12 +145,13 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_rsrc(uint64_t addr, in
 struct GridPos {
   int x, y, z;
 };
-__device__ __forceinline__ GridPos xcd_grouped() {
-  const uint32_t nx = gridDim.x, ny = gridDim.y;
-  const uint32_t total = nx * ny * gridDim.z;
-  uint32_t n = blockIdx.x + nx * (blockIdx.y + ny * blockIdx.z);
+__device__ __forceinline__ GridPos xcd_grouped(uint32_t n, uint32_t nx, uint32_t ny, uint32_t nz) {
+  const uint32_t total = nx * ny * nz;
   if (total % 8 == 0) n = (n % 8) * (total / 8) + n / 8;
   return GridPos{(int)(n % nx), (int)((n / nx) % ny), (int)(n / (nx * ny))};
+}
+__device__ __forceinline__ GridPos xcd_grouped() {
+  return xcd_grouped(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), gridDim.x, gridDim.y, gridDim.z);
 }
 
 // ------------------------------------------------------------- LDS-DMA

@@ -181,3 +181,35 @@ def test_transpose_wide(R, C, off):
     L.sppo_transpose_bf16(x, y[off:], R, C)
     torch.cuda.synchronize()
     assert torch.equal(y[off:off + R * C].view(C, R), x.view(R, C).t()) and (y[off + R * C:] == 3.0).all()
+
+
+# dK/dV and dQ in one launch (small grids; fp32 D = 64 always) against one after the other (with kernel
+# timing on, where they are separate launches): the same bits.  dQ in place of dO takes the separate launches.
+@pytest.mark.parametrize("dtype,B,S,N,Hq,Hkv,D", [("bf16", 1, 200, 2, 2, 1, 128), ("bf16", 1, 2047, 4, 4, 4, 128),
+                                                  ("bf16", 1, 1999, 2, 8, 8, 128), ("bf16", 2, 1001, 3, 4, 2, 64),
+                                                  ("bf16", 1, 65, 1, 1, 1, 64), ("f32", 2, 301, 3, 4, 2, 64)])
+def test_backward_pair_matches_separate_launches(dtype, B, S, N, Hq, Hkv, D):
+    announce(f"backward pair {dtype} B={B} S={S} N={N} H={Hq}/{Hkv} D={D}")
+    inp = make_inputs(B, S, Hq, Hkv, D, torch.bfloat16 if dtype == "bf16" else torch.float32, seed=7, device="cuda")
+    ca = ChunkedAttention(B, S, N, Hq, Hkv, D, dtype=dtype, offsets=[S * i // N for i in range(N + 1)])
+    outs = []
+    for timing in (False, True):
+        L.sppo_set_kernel_timing(ca.ctx, timing)
+        out = ca.alloc_outputs()
+        ca.step(inp, out)
+        torch.cuda.synchronize()
+        outs.append(out)
+    times = L.sppo_kernel_times(ca.ctx)
+    assert times["bwd_dkdv"]["launches"] == times["bwd_dq"]["launches"] == N
+    for key in ("o", "dq", "dk", "dv"):
+        assert torch.equal(outs[0][key], outs[1][key]), key
+    c0, c1 = ca.offsets[N - 1], ca.offsets[N]
+    q, do, o = [t[:, c0:c1].contiguous() for t in (inp["q"], inp["do"], outs[0]["o"])]
+    dk, dv = torch.empty_like(outs[0]["dk"]), torch.empty_like(outs[0]["dv"])
+    got = []
+    for dq in (torch.empty_like(q), do):  # the second call replaces dO
+        L.sppo_attn_bwd_chunk_noalloc(B, S, c0, c1, Hq, Hkv, D, dtype, 0.0, 0, q, inp["k"], inp["v"], o,
+                                      outs[0]["lse"][N - 1], do, dq, dk, dv)
+        torch.cuda.synchronize()
+        got.append((dq.clone(), dk.clone(), dv.clone()))
+    assert all(torch.equal(x, y) for x, y in zip(*got))
