@@ -40,6 +40,8 @@ the device (a HostPacer; 0 lets it run free).
 """
 from __future__ import annotations
 
+from contextlib import nullcontext
+
 import torch
 
 from . import sppo as L
@@ -76,6 +78,24 @@ class ChunkedAttention:
         if self.B == 1:
             return full[:, c0:c1]
         return full[:, c0:c1].contiguous()
+
+    def chunk_addrs(self, full):
+        """What the C entry points take for each chunk of a full tensor: its
+        address (B = 1), or a chunk-local copy (B > 1).  A tensor that does not
+        hold every chunk goes through chunk_view, whose empty views are refused."""
+        if self.B == 1 and full.numel() and full.shape[1] >= self.S:
+            p, row = full.data_ptr(), full.stride(1) * full.element_size()
+            return [p + c * row for c in self.offsets[:-1]]
+        return [self.chunk_view(full, i) for i in range(self.N)]
+
+    def chunk_outputs(self, full):
+        """The same for an output, of which a walk writes every row, and the
+        (view, buffer) pairs to copy back once it has (B > 1)."""
+        if self.B == 1:
+            return self.chunk_addrs(full), []
+        views = [full[:, self.offsets[i]:self.offsets[i + 1]] for i in range(self.N)]
+        bufs = [x if x.is_contiguous() else torch.empty_like(x, memory_format=torch.contiguous_format) for x in views]
+        return bufs, [(x, y) for x, y in zip(views, bufs) if x is not y]
 
     def alloc_outputs(self, export=True):
         """dq, dk, dv; with ``export`` also the full-length o and per-chunk
@@ -149,6 +169,8 @@ class ChunkedAttention:
         key = (offl, lookahead, rows)
         if self._layout != key:
             self._planes = [plane_layout(self.region_planes(i)) for i in range(self.N)]
+            self._shapes = [((self.B, n, self.Hq, self.D), (self.B, self.Hq, n))
+                            for n in map(self.chunk_len, range(self.N))]
             sizes = [size for _, size in self._planes]
             q = self.fwd_slots - 1  # a chunk's forward memory is reused fwd_slots chunks later
             cap, q = plan_capacity(walk_schedule(self.N, offl, lookahead), sizes, quarantine=q)
@@ -163,10 +185,10 @@ class ChunkedAttention:
     def _acquire(self, i, s):
         """Allocate chunk i's region; returns (offset, views of its planes)."""
         off = self.arena.acquire(self.ctx, s, self._planes[i][1], i)
-        B, Hq, D, n = self.B, self.Hq, self.D, self.chunk_len(i)
         po, dt, a = self._planes[i][0], self.torch_dtype, self.arena
-        return off, {"q": a.view(off + po["q"], (B, n, Hq, D), dt), "o": a.view(off + po["o"], (B, n, Hq, D), dt),
-                     "lse": a.view(off + po["lse"], (B, Hq, n), torch.float32)}
+        full, lse = self._shapes[i]
+        return off, {"q": a.view(off + po["q"], full, dt), "o": a.view(off + po["o"], full, dt),
+                     "lse": a.view(off + po["lse"], lse, torch.float32)}
 
     def step(self, inp, out, offload_chunks=None, lookahead=2, poison=False, stream=None, marks=None,
              export=None, finalize=None):
@@ -191,11 +213,12 @@ class ChunkedAttention:
         arena, keep = self.arena, self.keep
         arena.reset()
         s = torch.cuda.current_stream() if stream is None else stream
+        sp = getattr(s, "cuda_stream", s)  # the stream as the C entry points take it
+        on_stream = nullcontext if stream is None else lambda: torch.cuda.stream(s)
         q, k, v, do = inp["q"], inp["k"], inp["v"], inp["do"]
-        qc = [self.chunk_view(q, i) for i in range(self.N)]
-        dc = [self.chunk_view(do, i) for i in range(self.N)]
-        dqc = [self.chunk_view(out["dq"], i) for i in range(self.N)]
-        rows = self.offload_rows()
+        qc, dc = self.chunk_addrs(q), self.chunk_addrs(do)
+        dqc, unpack = self.chunk_outputs(out["dq"])
+        rows = self._layout[2]
 
         def mark(label):
             self.pacer.boundary(s)
@@ -207,22 +230,22 @@ class ChunkedAttention:
         held = {}  # chunk -> (region, views) of chunks that stay on the device
         for i in range(self.N):
             mark(("fwd", i))
-            slot, sv = self._acquire(i, s)
-            L.sppo_attn_fwd_chunk(self.ctx, i, qc[i], k, v, sv["o"], sv["lse"], s)
+            slot, sv = self._acquire(i, sp)
+            L.sppo_attn_fwd_chunk(self.ctx, i, qc[i], k, v, sv["o"], sv["lse"], sp)
             if export:
                 c0, c1 = self.offsets[i], self.offsets[i + 1]
-                with torch.cuda.stream(s):
+                with on_stream():
                     out["o"][:, c0:c1].copy_(sv["o"])
                     out["lse"][i].copy_(sv["lse"])
             if i in offl:
                 bufs = L.chunk_bufs(q=qc[i], o=sv["o"], lse=sv["lse"], k=k, v=v, keep=keep.ptr(i))
-                L.sppo_offload_issue(self.ctx, i, bufs, s)
+                L.sppo_offload_issue(self.ctx, i, bufs, sp)
                 arena.release(slot, after_offload=True)
                 if poison:
-                    L.sppo_offload_wait(self.ctx, i, s)
+                    L.sppo_offload_wait(self.ctx, i, sp)
                     r = rows[i] if keep.ptr(i) is None else self.chunk_len(i)
-                    with torch.cuda.stream(s):
-                        qc[i][:, :r].fill_(float("nan"))
+                    with on_stream():
+                        (self.chunk_view(q, i) if self.B == 1 else qc[i])[:, :r].fill_(float("nan"))
                         sv["o"].fill_(float("nan"))
                         sv["lse"].fill_(float("nan"))
             else:
@@ -232,49 +255,48 @@ class ChunkedAttention:
             if poison:
                 # The evicted K/V rows are dead once their copies have landed.
                 for j in kv_chunks:
-                    L.sppo_offload_wait(self.ctx, j, s)
-                with torch.cuda.stream(s):
+                    L.sppo_offload_wait(self.ctx, j, sp)
+                with on_stream():
                     for j in kv_chunks:
                         c0 = self.offsets[j]
                         k[:, c0:c0 + rows[j]].fill_(float("nan"))
                         v[:, c0:c0 + rows[j]].fill_(float("nan"))
             for j in kv_chunks:
-                L.sppo_prefetch_kv(self.ctx, j, k, v, s)
+                L.sppo_prefetch_kv(self.ctx, j, k, v, sp)
         pending = sorted(offl, reverse=True)
         back = {}  # chunk -> (region, views) of prefetched chunks
         nxt = 0
         for i in reversed(range(self.N)):
             while nxt < len(pending) and pending[nxt] >= i - lookahead:
                 j = pending[nxt]
-                slot, sv = self._acquire(j, s)
-                L.sppo_prefetch(self.ctx, j, L.chunk_bufs(q=sv["q"], o=sv["o"], lse=sv["lse"], keep=keep.ptr(j)), s)
+                slot, sv = self._acquire(j, sp)
+                L.sppo_prefetch(self.ctx, j, L.chunk_bufs(q=sv["q"], o=sv["o"], lse=sv["lse"], keep=keep.ptr(j)), sp)
                 back[j] = (slot, sv)
                 nxt += 1
             mark(("bwd", i))
             slot, sv = back.pop(i) if i in offl else held.pop(i)
             qi = sv["q"] if i in offl else qc[i]
             L.sppo_attn_bwd_chunk(self.ctx, i, qi, k, v, sv["o"], sv["lse"], dc[i], dqc[i],
-                                  out["dk"], out["dv"], s)
+                                  out["dk"], out["dv"], sp)
             arena.release(slot)
             if finalize is not None:
-                L.sppo_attn_finalize_chunk(self.ctx, i, out["dk"], out["dv"], finalize["dk"], finalize["dv"], s)
+                L.sppo_attn_finalize_chunk(self.ctx, i, out["dk"], out["dv"], finalize["dk"], finalize["dv"], sp)
         mark(("end", -1))
-        if self.B > 1:
-            with torch.cuda.stream(s):
-                for i in range(self.N):
-                    c0, c1 = self.offsets[i], self.offsets[i + 1]
-                    out["dq"][:, c0:c1].copy_(dqc[i])
+        if unpack:
+            with on_stream():
+                for view, buf in unpack:
+                    view.copy_(buf)
 
     def forward_only(self, inp, out, stream=None):
         """Forward over all chunks without offload; leaves the context ready
         for a new walk."""
         s = torch.cuda.current_stream() if stream is None else stream
-        oc = [self.chunk_view(out["o"], i) for i in range(self.N)]
+        sp = getattr(s, "cuda_stream", s)
+        oc, unpack = self.chunk_outputs(out["o"])
+        qc = self.chunk_addrs(inp["q"]) if self.B == 1 else None
         for i in range(self.N):
-            L.sppo_attn_fwd_chunk(self.ctx, i, self.chunk_view(inp["q"], i), inp["k"], inp["v"],
-                                  oc[i], out["lse"][i], s)
+            qi = qc[i] if qc else self.chunk_view(inp["q"], i)
+            L.sppo_attn_fwd_chunk(self.ctx, i, qi, inp["k"], inp["v"], oc[i], out["lse"][i], sp)
         L.sppo_reset(self.ctx)
-        if self.B > 1:
-            for i in range(self.N):
-                c0, c1 = self.offsets[i], self.offsets[i + 1]
-                out["o"][:, c0:c1].copy_(oc[i])
+        for view, buf in unpack:
+            view.copy_(buf)

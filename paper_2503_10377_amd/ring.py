@@ -32,11 +32,14 @@ chunks.
 """
 from __future__ import annotations
 
+import math
+
 import torch
 
 from . import sppo as L
 
 ALIGN = 256
+MAX_VIEWS = 4096  # views an arena keeps
 
 
 def _up(n: int) -> int:
@@ -192,6 +195,7 @@ class DeviceArena:
         self.quarantine = quarantine
         self.alloc_ = CircularAllocator(capacity)
         self.buf = torch.empty(max(_up(capacity), ALIGN), dtype=torch.uint8, device=device)
+        self._views = {}
 
     @property
     def nbytes(self) -> int:
@@ -224,11 +228,17 @@ class DeviceArena:
         self.alloc_.release(off, after_offload)
 
     def view(self, off: int, shape, dtype) -> torch.Tensor:
-        n = 1
-        for d in shape:
-            n *= int(d)
-        nbytes = n * torch.empty((), dtype=dtype).element_size()
-        return self.buf[off:off + nbytes].view(dtype).view(*shape)
+        # The buffer never moves and a walk asks for the same few regions every
+        # time, so the views are made once (three took 15 us of a chunk's host time).
+        shape = tuple(shape)
+        key = (off, shape, dtype)
+        t = self._views.get(key)
+        if t is None:
+            nbytes = math.prod(shape) * dtype.itemsize
+            if len(self._views) >= MAX_VIEWS:
+                self._views.clear()
+            t = self._views[key] = self.buf[off:off + nbytes].view(dtype).view(shape)
+        return t
 
 
 def plane_layout(planes: dict) -> tuple:

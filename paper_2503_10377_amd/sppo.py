@@ -171,14 +171,16 @@ def status_name(status: int) -> str:
 
 
 def _ptr(x) -> int | None:
-    if x is None:
-        return None
+    if x is None or type(x) is int:
+        return x
     if hasattr(x, "data_ptr"):
         return x.data_ptr()
     return int(x)
 
 
 def _stream(s) -> int | None:
+    if type(s) is int:
+        return s
     if s is None:
         import torch
 
