@@ -182,9 +182,9 @@ class ChunkedAttention:
             self._layout = key
         return self.arena.nbytes + self.keep.nbytes
 
-    def _acquire(self, i, s):
+    def _acquire(self, i, s, wait=True):
         """Allocate chunk i's region; returns (offset, views of its planes)."""
-        off = self.arena.acquire(self.ctx, s, self._planes[i][1], i)
+        off = self.arena.acquire(self.ctx, s, self._planes[i][1], i, wait)
         po, dt, a = self._planes[i][0], self.torch_dtype, self.arena
         full, lse = self._shapes[i]
         return off, {"q": a.view(off + po["q"], full, dt), "o": a.view(off + po["o"], full, dt),
@@ -269,7 +269,7 @@ class ChunkedAttention:
         for i in reversed(range(self.N)):
             while nxt < len(pending) and pending[nxt] >= i - lookahead:
                 j = pending[nxt]
-                slot, sv = self._acquire(j, sp)
+                slot, sv = self._acquire(j, sp, wait=keep.ptr(j) is not None)
                 L.sppo_prefetch(self.ctx, j, L.chunk_bufs(q=sv["q"], o=sv["o"], lse=sv["lse"], keep=keep.ptr(j)), sp)
                 back[j] = (slot, sv)
                 nxt += 1

@@ -138,11 +138,11 @@ class ChunkedLayer:
             self._layout = key
         return self.arena.nbytes + self.keep.nbytes
 
-    def _acquire(self, i, s, x=None):
+    def _acquire(self, i, s, x=None, wait=True):
         """Allocate chunk i's region; returns (offset, views of its saved
         tensors).  x_i is the caller's rows when given, else the region's x
         plane (where a prefetch puts it)."""
-        off = self.arena.acquire(self.ctx, s, self._planes[i][1], i)
+        off = self.arena.acquire(self.ctx, s, self._planes[i][1], i, wait)
         n, H, HqD = self.chunk_len(i), self.H, self.Hq * self.D
         bf, f32 = torch.bfloat16, torch.float32
         po = self._planes[i][0]
@@ -267,7 +267,7 @@ class ChunkedLayer:
         for i in reversed(range(self.N)):
             while nxt < len(pending) and pending[nxt] >= i - lookahead:
                 j = pending[nxt]
-                slot, vj = self._acquire(j, s)
+                slot, vj = self._acquire(j, s, wait=keep.ptr(j) is not None)
                 L.sppo_prefetch(self.ctx, j, self._bufs(vj, keep.ptr(j)), s)
                 back[j] = (slot, vj)
                 nxt += 1

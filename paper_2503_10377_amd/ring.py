@@ -11,9 +11,14 @@ The arena is one preallocated device buffer used as a circular allocator:
 each chunk's saved tensors get one contiguous region (its planes inside it,
 each on a 256-byte boundary), allocated when the chunk's forward produces
 them or when its prefetch brings them back, and released
-  * after the chunk's offload was issued: the next allocation that reuses
-    any of its bytes first makes the compute stream wait for that offload's
-    copies (``sppo_offload_wait``);
+  * after the chunk's offload was issued: the next forward allocation that
+    reuses any of its bytes first makes the compute stream wait for that
+    offload's copies (``sppo_offload_wait``).  A prefetch that moves no kept
+    rows writes its region on the host-to-device stream alone, which needs no
+    such wait: it waits there for its own chunk's offload, the chunks come back
+    last offloaded first, and both copy streams run in order, so every offload
+    has landed by then (the compute stream goes on with the last chunk's
+    backward meanwhile);
   * after the chunk's backward was enqueued: stream order alone protects it
     (a prefetch into it waits for everything enqueued before it).
 Allocations walk around the buffer in order, so the forward walk reuses the
@@ -188,8 +193,8 @@ def plan_capacity(schedule, sizes, quarantine) -> tuple:
 class DeviceArena:
     """The device buffer behind a CircularAllocator.  It takes the planner's
     decisions exactly (the same quarantine), so a walk that follows the
-    planned schedule never runs out of room; reusing a region released by
-    an offload first makes the stream wait for that offload."""
+    planned schedule never runs out of room; with ``wait``, reusing a region
+    released by an offload first makes the stream wait for that offload."""
 
     def __init__(self, capacity: int, device, quarantine: int):
         self.quarantine = quarantine
@@ -210,12 +215,12 @@ class DeviceArena:
         before whatever the next walk enqueues)."""
         self.alloc_.reset()
 
-    def acquire(self, ctx, stream, nbytes, chunk) -> int:
+    def acquire(self, ctx, stream, nbytes, chunk, wait=True) -> int:
         a = self.alloc_
         waited = set()
 
         def take(r):
-            if r.chunk not in waited:
+            if wait and r.chunk not in waited:
                 L.sppo_offload_wait(ctx, r.chunk, stream)
                 waited.add(r.chunk)
 

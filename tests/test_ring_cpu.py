@@ -125,3 +125,21 @@ def test_allocator_against_a_model(cap_blocks, q, ops):
             m[2], m[3] = ("offload" if offl else "free"), a.count
         assert a.in_use == sum(m[1] - m[0] for m in model if m[2] == "live")
         assert a.high_water >= a.in_use
+
+
+def test_prefetch_takes_an_offloaded_region_without_a_wait(monkeypatch):
+    """What that rests on: the copies back run in order and each waits for its
+    own chunk's offload, and the first of them is the last chunk offloaded."""
+    waits = []
+    monkeypatch.setattr(L, "sppo_offload_wait", lambda ctx, i, stream=None: waits.append(i))
+    a = R.DeviceArena(256, "cpu", quarantine=0)
+    a.release(a.acquire(None, None, 256, 0), after_offload=True)
+    assert a.acquire(None, None, 256, 0, wait=False) == 0 and waits == []
+    for n in range(2, 7):
+        for mask in range(1, 2**n):
+            offl = [i for i in range(n) if mask >> i & 1]
+            for lookahead in range(n):
+                ev = R.walk_schedule(n, offl, lookahead)
+                issued = [i for kind, i in ev if kind == "offload"]
+                back = [i for k, (kind, i) in enumerate(ev) if kind == "alloc" and ("alloc", i) in ev[:k]]
+                assert issued == offl and back == offl[::-1]
