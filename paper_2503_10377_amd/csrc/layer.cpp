@@ -3,6 +3,7 @@
 // host, enqueues its kernels on the given stream, and returns a status.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "sppo.h"
@@ -75,7 +76,9 @@ sppo_status sppo_layernorm_fwd(int64_t rows, int32_t H, const void* x, int64_t l
 
 size_t sppo_layernorm_bwd_workspace(int64_t rows, int32_t H) {
   if (rows <= 0 || H <= 0) return 0;
-  const int64_t per = ln_rows_per_block(rows), nb = (rows + per - 1) / per;
+  // The most workgroups any number of rows up to this one takes, so that a
+  // workspace for the largest chunk serves the smaller ones.
+  const int64_t nb = std::min<int64_t>((rows + kLnRowsPerBlock - 1) / kLnRowsPerBlock, kLnMaxBlocks);
   return (size_t)nb * 2 * (size_t)H * sizeof(float);
 }
 

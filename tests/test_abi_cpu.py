@@ -162,3 +162,9 @@ def test_headers_compile_as_c99_and_cxx(tmp_path):
         r = subprocess.run([cc, std, "-Wall", "-Wextra", "-Werror", "-pedantic", "-I", inc, "-c", str(f),
                             "-o", str(tmp_path / f"h_{ext}.o")], capture_output=True, text=True)
         assert r.returncode == 0, r.stderr
+
+
+def test_layernorm_workspace_grows_with_rows():
+    """A workspace sized for the largest chunk serves every smaller one."""
+    sizes = [L.sppo_layernorm_bwd_workspace(rows, 256) for rows in range(1, 40000)]
+    assert all(a <= b for a, b in zip(sizes, sizes[1:]))
