@@ -18,7 +18,9 @@ them or when its prefetch brings them back, and released
     such wait: it waits there for its own chunk's offload, the chunks come back
     last offloaded first, and both copy streams run in order, so every offload
     has landed by then (the compute stream goes on with the last chunk's
-    backward meanwhile);
+    backward meanwhile).  What such a prefetch did not wait for stays on record
+    for the bytes of the whole released region: a later allocation that the
+    compute stream writes makes that wait if it overlaps any of them;
   * after the chunk's backward was enqueued: stream order alone protects it
     (a prefetch into it waits for everything enqueued before it).
 Allocations walk around the buffer in order, so the forward walk reuses the
@@ -193,14 +195,16 @@ def plan_capacity(schedule, sizes, quarantine) -> tuple:
 class DeviceArena:
     """The device buffer behind a CircularAllocator.  It takes the planner's
     decisions exactly (the same quarantine), so a walk that follows the
-    planned schedule never runs out of room; with ``wait``, reusing a region
-    released by an offload first makes the stream wait for that offload."""
+    planned schedule never runs out of room; with ``wait``, reusing bytes of a
+    region released by an offload first makes the stream wait for that offload,
+    also where an allocation without ``wait`` took a part of them before."""
 
     def __init__(self, capacity: int, device, quarantine: int):
         self.quarantine = quarantine
         self.alloc_ = CircularAllocator(capacity)
         self.buf = torch.empty(max(_up(capacity), ALIGN), dtype=torch.uint8, device=device)
         self._views = {}
+        self._unwaited = []  # (start, end, chunk) of reused regions whose offload the stream may not be past
 
     @property
     def nbytes(self) -> int:
@@ -214,19 +218,20 @@ class DeviceArena:
         """Forget every region (between walks, once their work is ordered
         before whatever the next walk enqueues)."""
         self.alloc_.reset()
+        self._unwaited = []
 
     def acquire(self, ctx, stream, nbytes, chunk, wait=True) -> int:
         a = self.alloc_
-        waited = set()
-
-        def take(r):
-            if wait and r.chunk not in waited:
-                L.sppo_offload_wait(ctx, r.chunk, stream)
-                waited.add(r.chunk)
-
-        off = a.alloc(nbytes, chunk, lambda r: a.count - r.released_at >= self.quarantine, take)
+        off = a.alloc(nbytes, chunk, lambda r: a.count - r.released_at >= self.quarantine,
+                      lambda r: self._unwaited.append((r.start, r.end, r.chunk)))
         if off is None:
             raise RuntimeError(f"device arena of {self.nbytes} bytes is too small for chunk {chunk}")
+        if wait and self._unwaited:
+            end = off + _up(nbytes)
+            over = {c: None for lo, hi, c in self._unwaited if lo < end and hi > off}
+            for c in over:
+                L.sppo_offload_wait(ctx, c, stream)
+            self._unwaited = [r for r in self._unwaited if r[2] not in over]
         return off
 
     def release(self, off: int, after_offload: bool = False):

@@ -186,6 +186,21 @@ def test_partial_offload_rows(mode, B):
                                                             B * sum(rows) * (per_row - 2 * Hq * D * 2 - 4 * Hq))
 
 
+@pytest.mark.parametrize("mode", ["qol", "qkvol_evict"])
+def test_mixed_full_and_partial_rows_share_the_arena(mode):
+    """Unequal chunks, the late ones offloaded whole (their prefetches make no
+    wait) and the early ones in part (their kept rows are written on the
+    compute stream), without the waits of poisoning: the host copies are those
+    of the walk without offload, and so is every result."""
+    offsets = [0, 819, 1638, 2457, 3276, 4096]
+    rows = [300, 500, 819, 819, 820]
+    shape = (SHAPE["S"], 32, 8, 128)
+    ref = run("none", offsets=offsets, shape=shape, seed=13)[0]
+    for lookahead in (1, 2, 3):
+        res, _ = run(mode, offsets=offsets, shape=shape, seed=13, rows=rows, lookahead=lookahead)
+        assert_bitwise(ref, res)
+
+
 def test_offload_rows_errors():
     announce("offload rows errors")
     S, Hq, Hkv, D = 1024, 2, 2, 64

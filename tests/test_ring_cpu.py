@@ -143,3 +143,59 @@ def test_prefetch_takes_an_offloaded_region_without_a_wait(monkeypatch):
                 issued = [i for kind, i in ev if kind == "offload"]
                 back = [i for k, (kind, i) in enumerate(ev) if kind == "alloc" and ("alloc", i) in ev[:k]]
                 assert issued == offl and back == offl[::-1]
+
+
+def _partitions(n):
+    yield [8] * n
+    yield [8 + (i == n - 1) for i in range(n)]
+    yield [8 + (i == 0) for i in range(n)]
+    yield [8 + (-1) ** i for i in range(n)]
+    yield [12 - i for i in range(n)]  # longest first, as a FLOPs-balanced partition
+    yield [5 + 3 * (i % 3) for i in range(n)]
+
+
+@pytest.mark.parametrize("n", [2, 3, 4, 5, 6])
+@pytest.mark.parametrize("lookahead", [0, 1, 2, 3])
+@pytest.mark.parametrize("fwd_slots", [1, 2, 4])
+def test_kept_rows_never_land_on_an_offload_in_flight(monkeypatch, n, lookahead, fwd_slots):
+    """A prefetch with kept rows writes its region on the compute stream: that
+    stream has waited for every offload whose source bytes the region
+    overlaps, also where an earlier prefetch took a part of those bytes
+    without a wait.  Walks over unequal chunks, every mix of fully and partly
+    offloaded ones, the last chunk offloaded or not.  The compute stream is
+    past an offload once it waited for it or for a later one (the copies run
+    in order), and past all of them at the backward of a prefetched chunk."""
+    state = {}
+
+    def wait(ctx, i, stream=None):
+        state["past"] = max(state["past"], state["order"].index(i))
+
+    monkeypatch.setattr(L, "sppo_offload_wait", wait)
+    for parts in _partitions(n):
+        sizes = [R.ALIGN * x for x in parts]
+        for offl in (range(n - 1), range(n)):
+            cap, q = R.plan_capacity(R.walk_schedule(n, offl, lookahead), sizes, fwd_slots - 1)
+            arena = R.DeviceArena(cap, "meta", quarantine=q)
+            for mask in range(1 << len(offl)):
+                arena.reset()
+                keep = [bool(mask >> i & 1) for i in range(n)]
+                state.update(past=-1, order=[])
+                source, live = [], {}  # source: (start, end, place in the order) of each offload issued
+                for i in range(n):
+                    live[i] = arena.acquire(None, None, sizes[i], i)
+                    if i in offl:
+                        source.append((live[i], live[i] + sizes[i], len(state["order"])))
+                        state["order"].append(i)
+                        arena.release(live.pop(i), after_offload=True)
+                pending = sorted(offl, reverse=True)
+                for i in reversed(range(n)):
+                    while pending and pending[0] >= i - lookahead:
+                        j = pending.pop(0)
+                        live[j] = arena.acquire(None, None, sizes[j], j, wait=keep[j])
+                        if keep[j]:
+                            late = [k for lo, hi, k in source if lo < live[j] + sizes[j] and hi > live[j]
+                                    and k > state["past"]]
+                            assert not late, (parts, list(offl), keep, j, late)
+                    if i in offl:
+                        state["past"] = len(state["order"])
+                    arena.release(live.pop(i))
