@@ -505,17 +505,23 @@ hipError_t launch_bwd_pre_f32(const ChunkArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// One launch, or for more than 1.3e8 keys several: a launch's tiles and so
+// its results are those of one over all of them.
 hipError_t launch_bwd_dkdv_f32(const ChunkArgs& a, hipStream_t stream) {
   if (a.kv0 < 0 || a.kv1 > a.c1 || a.kv0 >= a.kv1) return hipErrorInvalidValue;
-  dim3 grid((unsigned)((a.kv1 - a.kv0 + kB - 1) / kB), (unsigned)a.Hkv, (unsigned)a.B);
-  if (a.D == 64) {
-    hipLaunchKernelGGL(dkdv_f32_kernel<64>, grid, dim3(512), 0, stream, a);
-  } else if (a.D == 128) {
-    hipLaunchKernelGGL(dkdv_f32_kernel<128>, grid, dim3(256), 0, stream, a);
-  } else {
-    return hipErrorInvalidValue;
+  if (a.D != 64 && a.D != 128) return hipErrorInvalidValue;
+  const int threads = 64 * (a.D == 64 ? kDkdvWaves<64> : kDkdvWaves<128>);
+  const int64_t most = kMaxWorkItems / threads * kB;
+  hipError_t e = hipSuccess;
+  ChunkArgs p = a;
+  for (; p.kv0 < a.kv1 && e == hipSuccess; p.kv0 = p.kv1) {
+    p.kv1 = a.kv1 - p.kv0 > most ? p.kv0 + most : a.kv1;
+    const dim3 grid((unsigned)((p.kv1 - p.kv0 + kB - 1) / kB), (unsigned)a.Hkv, (unsigned)a.B);
+    if (a.D == 64) hipLaunchKernelGGL(dkdv_f32_kernel<64>, grid, dim3(threads), 0, stream, p);
+    else hipLaunchKernelGGL(dkdv_f32_kernel<128>, grid, dim3(threads), 0, stream, p);
+    e = hipGetLastError();
   }
-  return hipGetLastError();
+  return e;
 }
 
 hipError_t launch_bwd_dq_f32(const ChunkArgs& a, hipStream_t stream) {
@@ -531,14 +537,15 @@ hipError_t launch_bwd_dq_f32(const ChunkArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// At any size where the workgroups are alike (us, pre + dK/dV + dQ, one after
-// the other -> pair: 4 heads, rows [0, 256) 23.9 -> 15.2, [768, 1024) 38.2 ->
-// 26.6; 8 heads, rows [1000, 2000) 196 -> 189; 16 heads, 2048 rows 542 -> 543).
+// Where the workgroups are alike, at any size that one dimension of a grid
+// holds (us, pre + dK/dV + dQ, one after the other -> pair: 4 heads, rows [0,
+// 256) 23.9 -> 15.2, [768, 1024) 38.2 -> 26.6; 8 heads, rows [1000, 2000) 196
+// -> 189; 16 heads, 2048 rows 542 -> 543).
 bool bwd_pair_f32(const ChunkArgs& a) {
   if (a.D != 64) return false;
   const int64_t s = a.c1 - a.c0;
   const int64_t groups = (s + kB - 1) / kB * a.Hq * a.B + (a.kv1 - a.kv0 + kB - 1) / kB * a.Hkv * a.B;
-  return groups <= 0x7fffffff && !dq_overwrites_inputs(a, 4);
+  return groups <= kMaxWorkItems / 512 && !dq_overwrites_inputs(a, 4);
 }
 
 hipError_t launch_bwd_pair_f32(const ChunkArgs& a, hipStream_t stream) {

@@ -13,6 +13,10 @@ namespace sppo {
 // the last context-free call (or of sppo_create).
 void set_thread_error(const std::string& msg);
 
+// HIP takes at most this many work items (workgroups times threads) along a
+// dimension of a grid.
+constexpr int64_t kMaxWorkItems = 0xffffffff;
+
 // Compute units of the current device (asked of the runtime once per device;
 // 256 if it does not say).
 int device_cus();

@@ -1,0 +1,69 @@
+"""Which kernels the launchers choose, and their grids, without a GPU
+(launch_plan.cpp records the launches instead of making them)."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2503_10377_amd import build as B
+from paper_2503_10377_amd import sppo as L
+
+ROOT = B.ROOT
+WORK_ITEMS = 1 << 32  # HIP takes fewer than this many work items along a dimension
+GRID_YZ = 65535
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    L.lib()
+    exe = str(tmp_path_factory.mktemp("plan") / "launch_plan")
+    cmd = [B.hipcc(), "-O1", "-std=c++17", "--offload-arch=gfx950", os.path.join(ROOT, "tests", "launch_plan.cpp"), "-I", B.INCLUDE,
+           "-I", B.CSRC, "-rdynamic", "-o", exe, "-L", B.PKG, "-l:libsppo.so", f"-Wl,-rpath,{B.PKG}"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+
+    def run(cases):
+        env = dict(os.environ, HIP_VISIBLE_DEVICES="-1")
+        out = subprocess.run([exe], input="\n".join(cases) + "\n", capture_output=True, text=True, env=env)
+        assert out.returncode == 0, out.stderr
+        lines = out.stdout.splitlines()
+        assert len(lines) == len(cases)
+        return [x if x in ("none", "error") else [_launch(g) for g in x.split(" ; ")] for x in lines]
+
+    return run
+
+
+def _launch(group):
+    name, *n = group.split()
+    n = list(map(int, n))
+    return {"kernel": name, "grid": tuple(n[:3]), "threads": n[3], "keys": tuple(n[4:])}
+
+
+def legal(launches):
+    return launches not in ("none", "error") and all(
+        0 < x["grid"][0] * x["threads"] < WORK_ITEMS and 0 < x["grid"][1] <= GRID_YZ and 0 < x["grid"][2] <= GRID_YZ
+        for x in launches)
+
+
+def test_fp32_backward_grids_stay_launchable(plan):
+    """Sizes whose tiles times threads pass 2^32: the pair of both gradient
+    kernels is then not taken, and dK/dV goes out over ranges of keys on the
+    tile grid that cover every key once."""
+    # batch 65535 x 8 heads x 256 rows: 9.4M workgroups of 512 in one dimension
+    big = "f32 65535 8 1 64 256 0 256"
+    pair, dkdv, dq = plan(["pair " + big, "dkdv " + big, "dq " + big])
+    assert pair == "none" and legal(dkdv) and legal(dq)
+    # one below the line and one at it
+    for n, taken in ((2**22 - 1, True), (2**22, False)):  # n tiles of each kind
+        p, = plan([f"pair f32 1 1 1 64 {16 * n} 0 {16 * n}"])
+        assert (p != "none") == taken and (not taken or legal(p))
+    for D in (64, 128):
+        for S, c0 in ((140_000_001, 140_000_000), (268_435_457, 268_435_000), (1000, 990)):
+            d, = plan([f"dkdv f32 1 1 1 {D} {S} {c0} {S}"])
+            assert legal(d)
+            at = 0
+            for x in d:
+                assert x["keys"][0] == at and at % 16 == 0
+                at = x["keys"][1]
+                assert x["grid"][0] == (at - x["keys"][0] + 15) // 16
+            assert at == S and (len(d) == 1) == ((S + 15) // 16 * x["threads"] < WORK_ITEMS)
