@@ -456,12 +456,14 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t stream) {
   // epilogue), in ns as measured.  At 256 CUs: 1000 x 1024 x 4096 takes 69 /
   // 31 / 17 us on 256 / 128 / 64 tiles, 1000 x 4096 x 1024 (GELU) 34 / 17 / 24,
   // 2500 x 9216 x 2304 105 / 130 / 220, 4000 x 2048 x 8192 133 / 140 / 212.
+  // Tile rows are a grid's second dimension, which holds kMaxGridYZ of them.
   struct Option { int bt; double kb, fixed; };
   constexpr Option kTiles[3] = {{256, 1000, 8000}, {128, 500, 6000}, {64, 230, 2500}};
   const double cus = device_cus(), nkb = (double)((g.K + GBK - 1) / GBK);
   int bt = 0;
   double best = 0;
   for (const Option& t : kTiles) {
+    if (bt && (g.M + t.bt - 1) / t.bt > kMaxGridYZ) continue;
     const double tiles = (double)((g.M + t.bt - 1) / t.bt) * (double)((g.N + t.bt - 1) / t.bt);
     const double ns = __builtin_ceil(tiles / cus) * (nkb * t.kb + t.fixed);
     if (!bt || ns < best) {

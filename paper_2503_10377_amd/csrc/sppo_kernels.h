@@ -14,8 +14,8 @@ namespace sppo {
 void set_thread_error(const std::string& msg);
 
 // HIP takes at most this many work items (workgroups times threads) along a
-// dimension of a grid.
-constexpr int64_t kMaxWorkItems = 0xffffffff;
+// dimension of a grid, and this many workgroups along the second and third.
+constexpr int64_t kMaxWorkItems = 0xffffffff, kMaxGridYZ = 65535;
 
 // Compute units of the current device (asked of the runtime once per device;
 // 256 if it does not say).

@@ -67,3 +67,16 @@ def test_fp32_backward_grids_stay_launchable(plan):
                 at = x["keys"][1]
                 assert x["grid"][0] == (at - x["keys"][0] + 15) // 16
             assert at == S and (len(d) == 1) == ((S + 15) // 16 * x["threads"] < WORK_ITEMS)
+
+
+@pytest.mark.parametrize("tn", [0, 1])
+def test_gemm_tiles_fit_the_grid(plan, tn):
+    """Tall products whose time estimate favours small tiles keep to a tile
+    whose rows fit a grid dimension."""
+    cases = [f"gemm {tn} 0 {M} {N} {K}" for M in (65535 * 64, 65535 * 64 + 256, 6_000_128, 65535 * 128 + 256, 65535 * 256)
+             for N in (256 if tn else 4, 256) for K in (64, 1664, 4096, 16384)]
+    plans = plan(cases)
+    for c, p in zip(cases, plans):
+        assert legal(p) and len(p) == 1, c
+    if not tn:  # the small tile is the choice up to the limit
+        assert plan(["gemm 0 0 4194240 64 4096"])[0][0]["grid"][1] == 65535
