@@ -28,7 +28,7 @@ COMMON = [
     "-I", INCLUDE, "-I", CSRC, "-Wall", "-Wno-unused-function",
 ]
 
-# Per-source extra flags.  The attention kernels keep their MFMA
+# Per-source extra flags.  The attention and GEMM kernels keep their MFMA
 # results in arch VGPRs (the softmax reads S and dP with VALU ops, which would
 # otherwise copy them out of AGPRs one register at a time); the compiler then
 # places read-only MFMA operands (K/V or Q/dO fragments) in AGPRs.
@@ -37,6 +37,7 @@ EXTRA = {
     "gemm_bf16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "attn_fwd_bf16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "attn_bwd_bf16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "attn_bwd_bf16_mfma32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
 }
 
 

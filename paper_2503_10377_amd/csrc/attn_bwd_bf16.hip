@@ -29,29 +29,19 @@
 // a time, outside the pipeline.  Grids too small for the chip take the split
 // kernels further down.
 //
-// Every product is the 16x16x32 MFMA: per step as many cycles of the matrix
-// pipe as with 32x32x16, for less energy, and the LSE2 / Delta records take
-// half the LDS reads.  At the power limit the clock rose (dK/dV 1.89 -> 2.11
-// GHz, dQ 1.81 -> 2.11 at 32K tokens x 32 heads) while the lone wave on each
-// SIMD, which now issues twice the MFMAs, keeps the matrix pipe less busy (0.60
-// -> 0.53, 0.64 -> 0.56): dK/dV -1.2%, dQ -3.1% at 128K, both -5% at D = 64.
-// What is left is the one wave's instruction stream: moving half the
-// exponentials from the S/dP phase to the gradient phase changed nothing.
+// The products here are 16x16x32 MFMAs; the wide dK/dV of head size 128 is in
+// attn_bwd_bf16_mfma32.hip on 32x32x16.  Both occupy the matrix pipe for as
+// many cycles a step.  The smaller form takes less energy, so the clock rises,
+// but the lone wave on each SIMD issues twice the MFMAs: wide kernels with room
+// on the matrix pipe gain (D = 64: dK/dV 1-3%, dQ up to 5%), others lose.  What
+// is left is the one wave's instruction stream: moving half the exponentials
+// from the S/dP phase to the gradient phase changed nothing.
+#include "bwd_tiles.h"
 #include "sppo_kernels.h"
 #include "tile_common.h"
 
 namespace sppo {
 namespace {
-
-constexpr int kKvKeys = 128;  // keys per dK/dV workgroup (4 waves x 32)
-constexpr int kDqRows = 128;  // query rows per dQ workgroup (4 waves x 32)
-constexpr int kSB = 32;       // rows (dK/dV) or keys (dQ) per sub-block
-constexpr int kRing = 6;      // LDS ring slots
-constexpr int kAhead = 5;     // sub-blocks loaded ahead of the one in use
-// Each step's barrier also waits for sub-block n+2, so the B phase of step n
-// can read A(n+1)'s first natural operands in its last MFMA slots (which read
-// nothing else), and A's last slots read B's first transposed operands.
-static_assert(kAhead == kRing - 1, "a slot is refilled right after its last reader");
 
 // S or dP of a 32 x 32 sub-block: 16 x 16 tiles, [row tile][column tile].
 struct S4 {
@@ -92,8 +82,8 @@ __global__ __launch_bounds__(256) void bwd_pre_bf16_kernel(ChunkArgs a) {
 }
 
 // ------------------------------------------------------------------ dK dV
-template <int D>
 __global__ __launch_bounds__(256, 1) void bwd_dkdv_bf16_kernel(ChunkArgs a) {
+  constexpr int D = 64;
   using T = Tile<D>;
   constexpr int P = T::P, NK = D / 32, ND = D / 16;  // k-steps of S and dP, d tiles
   constexpr int IPWQ = (kSB / T::RPI) / 4;  // DMA instructions per wave per tensor per sub-block
@@ -248,10 +238,10 @@ __global__ __launch_bounds__(256, 1) void bwd_dkdv_bf16_kernel(ChunkArgs a) {
     rem -= kSB;
   };
   // Natural operand of the 16 rows 16 t.. of a sub-block, k-step kk, and
-  // transposed operand of its 32 rows, d tile dt (D = 64: rows 16.. swap the
-  // two k-steps' chunks and column blocks dt, dt ^ 2).
-  auto nat_rd = [&](const uint16_t* X, int t, int kk) { return ld_nat(X + 16 * t * P, nat[D == 64 ? kk ^ t : kk]); };
-  auto tr_rd = [&](const uint16_t* X, int dt) { return ld_tr(X, tro[dt], tro[D == 64 ? dt ^ 2 : dt] + 16 * P); };
+  // transposed operand of its 32 rows, d tile dt (rows 16.. swap the two
+  // k-steps' chunks and column blocks dt, dt ^ 2).
+  auto nat_rd = [&](const uint16_t* X, int t, int kk) { return ld_nat(X + 16 * t * P, nat[kk ^ t]); };
+  auto tr_rd = [&](const uint16_t* X, int dt) { return ld_tr(X, tro[dt], tro[dt ^ 2] + 16 * P); };
   // LSE2 and -Delta (the initial value of the dP accumulators) of this lane's
   // rows 16 qt + 4 g + 0..3 of a sub-block, from its record.
   auto rec_rd = [&](const float* ld, int qt) { return *reinterpret_cast<const f32x4*>(ld + 16 * qt + 4 * g); };
@@ -1223,13 +1213,12 @@ hipError_t launch_bwd_pre_bf16(const ChunkArgs& a, hipStream_t stream) {
 }
 
 // Workgroups of the persistent dK/dV kernel that one CU holds at once (its
-// registers allow one; asked of the runtime once per head size).
-template <int D>
-int dkdv_groups_per_cu() {
+// registers allow one; asked of the runtime once).
+static int dkdv_groups_per_cu() {
   static const int n = [] {
     int b = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, reinterpret_cast<const void*>(&bwd_dkdv_bf16_kernel<D>),
-                                                     256, 0) != hipSuccess || b < 1) {
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, reinterpret_cast<const void*>(&bwd_dkdv_bf16_kernel), 256,
+                                                     0) != hipSuccess || b < 1) {
       b = 1;
     }
     return b;
@@ -1267,14 +1256,10 @@ hipError_t launch_bwd_dkdv_bf16(const ChunkArgs& a, hipStream_t stream) {
     else hipLaunchKernelGGL((bwd_dkdv_split_kernel<128, 2, 2>), grid, dim3(256), 0, stream, a);
     return hipGetLastError();
   }
+  if (a.D == 128) return launch_bwd_dkdv_mfma32(a, tiles, stream);
   // persistent: as many workgroups as the CUs hold at once
-  const int64_t slots = (int64_t)a.n_cu * (a.D == 128 ? dkdv_groups_per_cu<128>() : dkdv_groups_per_cu<64>());
-  dim3 grid((unsigned)(tiles < slots ? tiles : slots));
-  if (a.D == 128) {
-    hipLaunchKernelGGL(bwd_dkdv_bf16_kernel<128>, grid, dim3(256), 0, stream, a);
-  } else {
-    hipLaunchKernelGGL(bwd_dkdv_bf16_kernel<64>, grid, dim3(256), 0, stream, a);
-  }
+  const int64_t slots = (int64_t)a.n_cu * dkdv_groups_per_cu();
+  hipLaunchKernelGGL(bwd_dkdv_bf16_kernel, dim3((unsigned)(tiles < slots ? tiles : slots)), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 

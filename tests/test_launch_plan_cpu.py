@@ -80,3 +80,17 @@ def test_gemm_tiles_fit_the_grid(plan, tn):
         assert legal(p) and len(p) == 1, c
     if not tn:  # the small tile is the choice up to the limit
         assert plan(["gemm 0 0 4194240 64 4096"])[0][0]["grid"][1] == 65535
+
+
+def kernels(p):
+    return [x["kernel"] for x in p]
+
+
+@pytest.mark.parametrize("heads", ["4 4", "8 2", "16 4", "32 8", "32 32"])
+def test_wide_dkdv_by_head_size(plan, heads):
+    """Wide dK/dV launches take the 32x32x16 kernel at head size 128 and the
+    16x16x32 one at 64, whatever the grid."""
+    for c0, c1 in ((0, 20000), (16300, 19059), (122880, 131072)):
+        for D, name in ((128, "bwd_dkdv_mfma32_kernel"), (64, "bwd_dkdv_bf16_kernel")):
+            p, = plan([f"dkdv bf16 1 {heads} {D} {c1} {c0} {c1}"])
+            assert legal(p) and name in kernels(p)[0] and p[0]["grid"][0] <= 256
