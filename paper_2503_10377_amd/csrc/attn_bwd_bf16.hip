@@ -29,13 +29,13 @@
 // a time, outside the pipeline.  Grids too small for the chip take the split
 // kernels further down.
 //
-// The products here are 16x16x32 MFMAs; the wide dK/dV of head size 128 is in
-// attn_bwd_bf16_mfma32.hip on 32x32x16.  Both occupy the matrix pipe for as
+// The products here are 16x16x32 MFMAs; the wide kernels of head size 128 are
+// in attn_bwd_bf16_mfma32.hip on 32x32x16.  Both occupy the matrix pipe for as
 // many cycles a step.  The smaller form takes less energy, so the clock rises,
-// but the lone wave on each SIMD issues twice the MFMAs: wide kernels with room
-// on the matrix pipe gain (D = 64: dK/dV 1-3%, dQ up to 5%), others lose.  What
-// is left is the one wave's instruction stream: moving half the exponentials
-// from the S/dP phase to the gradient phase changed nothing.
+// but the lone wave on each SIMD issues twice the MFMAs: at D = 64, with half
+// the MFMAs per exponential, that gains (dK/dV 1-3%, dQ up to 5%), at 128 it
+// loses.  What is left is the one wave's instruction stream: moving half the
+// exponentials from the S/dP phase to the gradient phase changed nothing.
 #include "bwd_tiles.h"
 #include "sppo_kernels.h"
 #include "tile_common.h"
@@ -507,8 +507,8 @@ __global__ __launch_bounds__(256, 1) void bwd_dkdv_bf16_kernel(ChunkArgs a) {
 }
 
 // --------------------------------------------------------------------- dQ
-template <int D>
 __global__ __launch_bounds__(256, 1) void bwd_dq_bf16_kernel(ChunkArgs a) {
+  constexpr int D = 64;
   using T = Tile<D>;
   constexpr int P = T::P, NK = D / 32, ND = D / 16;  // k-steps of S and dP, d tiles
   constexpr int IPWK = (kSB / T::RPI) / 4;  // DMA instructions per wave per tensor per sub-block
@@ -604,8 +604,8 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_bf16_kernel(ChunkArgs a) {
     va += sbb;
     remk -= kSB;
   };
-  auto nat_rd = [&](const uint16_t* X, int t, int kk) { return ld_nat(X + 16 * t * P, nat[D == 64 ? kk ^ t : kk]); };
-  auto tr_rd = [&](const uint16_t* X, int dt) { return ld_tr(X, tro[dt], tro[D == 64 ? dt ^ 2 : dt] + 16 * P); };
+  auto nat_rd = [&](const uint16_t* X, int t, int kk) { return ld_nat(X + 16 * t * P, nat[kk ^ t]); };
+  auto tr_rd = [&](const uint16_t* X, int dt) { return ld_tr(X, tro[dt], tro[dt ^ 2] + 16 * P); };
   // Natural operand o of a sub-block: k-step o / 4, key tile (o / 2) % 2, K (o even) or V (o odd).
   auto nat_of = [&](const uint16_t* K, int o) { return nat_rd((o & 1) ? K + kSB * P : K, (o >> 1) & 1, o >> 2); };
   // The MFMA of query tile qt that operand o feeds: S^T = K Q^T or dP^T - Delta = V dO^T - Delta (lane <-> query).
@@ -1280,10 +1280,11 @@ hipError_t launch_bwd_dq_bf16(const ChunkArgs& a, hipStream_t stream) {
     const dim3 grid((unsigned)((s + 63) / 64), (unsigned)a.Hq, (unsigned)a.B);
     if (a.D == 128) hipLaunchKernelGGL(bwd_dq_split_kernel<128>, grid, dim3(512), 0, stream, a);
     else hipLaunchKernelGGL(bwd_dq_split_kernel<64>, grid, dim3(512), 0, stream, a);
+  } else if (a.D == 128) {
+    return launch_bwd_dq_mfma32(a, stream);
   } else {
     const dim3 grid((unsigned)((s + kDqRows - 1) / kDqRows), (unsigned)a.Hq, (unsigned)a.B);
-    if (a.D == 128) hipLaunchKernelGGL(bwd_dq_bf16_kernel<128>, grid, dim3(256), 0, stream, a);
-    else hipLaunchKernelGGL(bwd_dq_bf16_kernel<64>, grid, dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(bwd_dq_bf16_kernel, grid, dim3(256), 0, stream, a);
   }
   return hipGetLastError();
 }

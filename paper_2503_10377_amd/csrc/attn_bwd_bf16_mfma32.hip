@@ -1,15 +1,21 @@
-// The wide dK/dV kernel of the bf16 backward for head size 128, on 32x32x16
-// MFMAs; the work, the LDS ring and the pipeline are those of the 16x16x32
-// kernels of attn_bwd_bf16.hip.
+// The wide kernels of the bf16 backward for head size 128, dK/dV and dQ, on
+// 32x32x16 MFMAs; the work, the LDS ring and the pipeline are those of the
+// 16x16x32 kernels of attn_bwd_bf16.hip.
 //
-// Why the larger MFMA here: with one wave per SIMD the kernel is bound by that
-// wave's instruction stream, and 16x16x32 issues twice the MFMAs.  Measured in
-// turn with a 16x16x32 form on two machines (us, 32x32x16 against 16x16x32):
-// 4 heads, 6000 rows 158 / 172; 8/2 heads, rows [16300, 19059) 549 / 577; 16/4
-// heads, rows [4096, 8192) 403 / 424; 32 heads, rows [28672, 32768) 3540 /
-// 3708, [57344, 65536) 13901 / 14435, [122880, 131072) 28340 / 28742; the
-// other way by 2% in a few (8 heads, rows [10000, 20000) 1034 / 1016).  At
-// head size 64 the smaller form is 1-3% the faster.
+// Why the larger MFMA here: with one wave per SIMD the kernels are bound by
+// that wave's instruction stream, and 16x16x32 issues twice the MFMAs.
+// Measured in turn with 16x16x32 forms on three machines (us, 32x32x16 /
+// 16x16x32):
+//   dK/dV  4 heads, 6000 rows 158 / 172; 8/2 heads, rows [16300, 19059) 549 /
+//          577; 16/4 heads, rows [4096, 8192) 403 / 424; 32 heads, rows [28672,
+//          32768) 3540 / 3708, [57344, 65536) 13901 / 14435, [122880, 131072)
+//          28340 / 28742; the other way by 2% in a few (8 heads, rows [10000,
+//          20000) 1034 / 1016)
+//   dQ     4 heads, 6000 rows 100 / 112; 8/2 heads, rows [16300, 19059) 304 /
+//          335; 32 heads, 2048 rows 73 / 78, rows [2048, 4096) 158 / 161; in
+//          larger grids between 4% less and 4% more, machine to machine (32
+//          heads, rows [122880, 131072) 20.43 / 21.26 ms, 20.76 / 19.98)
+// At head size 64 the smaller form is 1-3% the faster.
 #include "bwd_tiles.h"
 #include "mfma32.h"
 #include "sppo_kernels.h"
@@ -450,6 +456,256 @@ __global__ __launch_bounds__(256, 1) void bwd_dkdv_mfma32_kernel(ChunkArgs a) {
   }
 }
 
+// --------------------------------------------------------------------- dQ
+__global__ __launch_bounds__(256, 1) void bwd_dq_mfma32_kernel(ChunkArgs a) {
+  using T = Tile32;
+  constexpr int D = T::D, P = T::P, NK = D / 16, ND = D / 32;
+  constexpr int IPWK = (kSB / T::RPI) / 4;  // DMA instructions per wave per tensor per sub-block
+  static_assert(IPWK >= 1 && IPWK * 4 * T::RPI == kSB, "sub-block splits over 4 waves");
+  constexpr int DMA_PER_SB = 2 * IPWK;
+  // One LDS object per ring slot: [K rows | V rows].
+  constexpr int SLOT = 2 * kSB * P;
+  __shared__ __attribute__((aligned(1024))) uint16_t R0[SLOT], R1[SLOT], R2[SLOT], R3[SLOT], R4[SLOT], R5[SLOT];
+  auto slot = [&](auto I) -> uint16_t* {
+    constexpr int i = decltype(I)::value;
+    if constexpr (i == 0) return R0; else if constexpr (i == 1) return R1; else if constexpr (i == 2) return R2;
+    else if constexpr (i == 3) return R3; else if constexpr (i == 4) return R4; else return R5;
+  };
+  auto slot_rt = [&](int i) -> uint16_t* {
+    return i == 0 ? R0 : i == 1 ? R1 : i == 2 ? R2 : i == 3 ? R3 : i == 4 ? R4 : R5;
+  };
+
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, g = lane >> 5;
+  const GridPos gp = xcd_grouped();  // the query tiles of a head behind one L2
+  const int t = gridDim.x - 1 - gp.x;  // longest (latest) query tiles first
+  const int h = gp.y;
+  const int64_t b = gp.z;
+  const int hk = h / (a.Hq / a.Hkv);
+  const int64_t c0 = a.c0, c1 = a.c1, s = c1 - c0;
+  const int64_t q0 = c0 + (int64_t)t * kDqRows;
+  const int64_t r = q0 + 32 * w + l32;
+  const bool rvalid = r < c1;
+  const int64_t kend = (q0 + kDqRows < c1) ? q0 + kDqRows : c1;
+  const int nsub = (int)((kend + kSB - 1) / kSB);
+  const int N = (int)(q0 / kSB);  // key sub-blocks every row of the workgroup sees in full
+  const float C = a.scale * kLog2e;
+
+  int nat[NK];
+#pragma unroll
+  for (int kk = 0; kk < NK; ++kk) nat[kk] = T::nat(lane, kk);
+  int tro[ND][2];
+#pragma unroll
+  for (int db = 0; db < ND; ++db) {
+    tro[db][0] = T::tr(lane, db, 0);
+    tro[db][1] = T::tr(lane, db, 1);
+  }
+  const int64_t kvstride = (int64_t)a.Hkv * D;
+  int dmak[IPWK];
+#pragma unroll
+  for (int x = 0; x < IPWK; ++x) dmak[x] = T::dma(lane, w * IPWK + x, kvstride);
+  const uint16_t* kbase = static_cast<const uint16_t*>(a.k) + (b * a.S * a.Hkv + hk) * D;
+  const uint16_t* vbase = static_cast<const uint16_t*>(a.v) + (b * a.S * a.Hkv + hk) * D;
+
+  bf16x8 qf[NK], df[NK];
+  float lse2 = INFINITY, ndl = 0.f;  // a padding row gets P = 0
+  if (rvalid) {
+    const int64_t off = ((b * s + (r - c0)) * a.Hq + h) * D;
+    const uint16_t* qrow = static_cast<const uint16_t*>(a.q) + off;
+    const uint16_t* drow = static_cast<const uint16_t*>(a.dout) + off;
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk) {
+      qf[kk] = as_bf16x8(ld_global16(qrow + 16 * kk + 8 * g));
+      df[kk] = as_bf16x8(ld_global16(drow + 16 * kk + 8 * g));
+    }
+    lse2 = a.lse2[(b * a.Hq + h) * s + (r - c0)];
+    ndl = a.delta[(b * a.Hq + h) * s + (r - c0)];
+  } else {
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk) qf[kk] = df[kk] = bf16x8{};
+  }
+  f32x16 dq[ND];
+#pragma unroll
+  for (int db = 0; db < ND; ++db) dq[db] = f32x16{};
+  // -Delta of the lane's row in every element: the initial value of each dP^T
+  // accumulator, so the MFMAs produce dP^T - Delta.
+  f32x16 ninit;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) ninit[v] = ndl;
+
+  // DMA of K/V sub-block u (keys [32u, 32u+32)) into a slot; keys past the
+  // chunk end load zeros, so every call issues DMA_PER_SB instructions.
+  // Sub-blocks are issued in key order, so scalar state walks K and V one
+  // sub-block per call.
+  const int64_t sbb = (int64_t)kSB * kvstride * 2;  // bytes per sub-block of K or V
+  const int krow_bytes = (int)(kvstride * 2);
+  uint64_t ka = uniform_u64(reinterpret_cast<uint64_t>(kbase)), va = uniform_u64(reinterpret_cast<uint64_t>(vbase));
+  int remk = (int)c1;  // keys [k0, c1) are valid
+  auto issue_next = [&](uint16_t* dst) {
+    const int n = remk <= 0 ? 0 : (remk < kSB ? remk : kSB);
+    const auto rk = uniform_rsrc(ka, n * krow_bytes);
+    const auto rv = uniform_rsrc(va, n * krow_bytes);
+#pragma unroll
+    for (int x = 0; x < IPWK; ++x) {
+      lds_dma16(rk, dst + (w * IPWK + x) * 512, dmak[x]);
+      lds_dma16(rv, dst + kSB * P + (w * IPWK + x) * 512, dmak[x]);
+    }
+    ka += sbb;
+    va += sbb;
+    remk -= kSB;
+  };
+  auto tr_rd = [&](const uint16_t* X, int hh, int db) {
+    return ld_tr(X, tro[db][0] + 16 * hh * P, tro[db][1] + 16 * hh * P);
+  };
+  // S^T = K Q^T and dP^T - Delta = V dO^T - Delta of one sub-block (lane <-> query).
+  auto sdp = [&](const uint16_t* K, f32x16& sv, f32x16& dp) {
+    const uint16_t* V = K + kSB * P;
+    sv = mfma32(ld_nat(K, nat[0]), qf[0], f32x16{});
+    dp = mfma32(ld_nat(V, nat[0]), df[0], ninit);
+#pragma unroll
+    for (int kk = 1; kk < NK; ++kk) {
+      sv = mfma32(ld_nat(K, nat[kk]), qf[kk], sv);
+      dp = mfma32(ld_nat(V, nat[kk]), df[kk], dp);
+    }
+  };
+
+  // Prologue: sub-blocks 0..4 (which also covers every diagonal sub-block
+  // when N is 0).
+  issue_next(R0);
+  issue_next(R1);
+  issue_next(R2);
+  issue_next(R3);
+  issue_next(R4);
+
+  if (N > 0) {
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm((kAhead - 2) * DMA_PER_SB));
+    __syncthreads();
+    f32x16 sa, da, sb2, db2;
+    sdp(R0, sa, da);
+    bf16x8 opn[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) opn[m] = ld_nat((m & 1) ? R1 + kSB * P : R1, nat[m >> 1]);
+    // Step n in slot I: A(n) reads slot I+1 (natural K, V); B(n) reads slot I
+    // (transposed K) and, in its last MFMA slots, A(n+1)'s first natural
+    // operands from slot I+2.  At its start sub-blocks n+1 and n+2 have
+    // landed; then sub-block n+5 goes to slot I+5 = I-1, free since step n-1.
+    auto step = [&](auto sl, f32x16& scur, f32x16& dcur, f32x16& snext, f32x16& dnext) {
+      constexpr int I = decltype(sl)::value;
+      constexpr int I1 = (I + 1) % kRing, I2 = (I + 2) % kRing, I5 = (I + kAhead) % kRing;
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm((kAhead - 3) * DMA_PER_SB));
+      __syncthreads();
+      issue_next(slot(IC<I5>{}));  // sub-block n + kAhead
+      const uint16_t* Kn = slot(IC<I1>{});
+      const uint16_t* Vn = Kn + kSB * P;
+      const uint16_t* Kc = slot(IC<I>{});
+      // A(n): MFMA m (NA of them) is S^T(n+1) (m even) or dP^T(n+1) (m odd),
+      // k-step m/2; its operand is read four MFMAs ahead.  The VALU turns the
+      // 16 elements of S^T(n), dP^T(n) into dS^T(n), element i beside MFMA
+      // i / (16 / NA).
+      constexpr int NA = 2 * NK, EPM = 16 / NA;
+      auto nat_op = [&](int m) { return ld_nat((m & 1) ? Vn : Kn, nat[m >> 1]); };
+      bf16x8 op[NA];
+#pragma unroll
+      for (int m = 0; m < 4; ++m) op[m] = opn[m];
+      float pv[16], ds[16];
+      bf16x8 dsb[2];
+      // B(n): MFMA jj is dQ^T d-block jj % ND for k-half jj / ND; its
+      // transposed K operand is read three slots ahead (the first three in
+      // the last MFMA slots of A(n)).
+      constexpr int NB = 2 * ND;
+      auto tr_op = [&](int jj) { return tr_rd(Kc, jj / ND, jj % ND); };
+      bf16x8 top[NB];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        if (i % EPM == 0) {
+          const int mi = i / EPM;
+          if (mi & 1) {
+            dnext = mfma32(op[mi], df[mi >> 1], mi == 1 ? ninit : dnext);
+          } else {
+            snext = mfma32(op[mi], qf[mi >> 1], mi == 0 ? f32x16{} : snext);
+          }
+          if (mi + 4 < NA) op[mi + 4] = nat_op(mi + 4);
+          else if (mi + 4 - NA < 3) top[mi + 4 - NA] = tr_op(mi + 4 - NA);
+        }
+        // Element i's exp, element i-1's dS (no exp result read right away).
+        pv[i] = fast_exp2(scur[i] * C - lse2);
+        if (i > 0) ds[i - 1] = pv[i - 1] * dcur[i - 1];
+        if (i == 8) dsb[0] = pack_bf16x8(ds[0], ds[1], ds[2], ds[3], ds[4], ds[5], ds[6], ds[7]);
+        if (i % EPM == EPM - 1) __builtin_amdgcn_sched_barrier(0);
+      }
+      ds[15] = pv[15] * dcur[15];
+      dsb[1] = pack_bf16x8(ds[8], ds[9], ds[10], ds[11], ds[12], ds[13], ds[14], ds[15]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int jj = 0; jj < NB; ++jj) {
+        dq[jj % ND] = mfma32(top[jj], dsb[jj / ND], dq[jj % ND]);
+        if (jj + 3 < NB) {
+          top[jj + 3] = tr_op(jj + 3);
+        } else {  // A(n+1)'s first natural operands, from sub-block n+2
+          const uint16_t* K2 = slot(IC<I2>{});
+          const int m0 = jj + 3 - NB;
+          opn[m0] = ld_nat((m0 & 1) ? K2 + kSB * P : K2, nat[m0 >> 1]);
+          if (m0 == 2) opn[3] = ld_nat(K2 + kSB * P, nat[1]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    for (int n = 0; n < N; n += kRing) {
+      step(IC<0>{}, sa, da, sb2, db2);
+      if (n + 1 >= N) break;
+      step(IC<1>{}, sb2, db2, sa, da);
+      if (n + 2 >= N) break;
+      step(IC<2>{}, sa, da, sb2, db2);
+      if (n + 3 >= N) break;
+      step(IC<3>{}, sb2, db2, sa, da);
+      if (n + 4 >= N) break;
+      step(IC<4>{}, sa, da, sb2, db2);
+      if (n + 5 >= N) break;
+      step(IC<5>{}, sb2, db2, sa, da);
+    }
+  }
+
+  // Diagonal sub-blocks [N, nsub) (at most five): already in the ring, since
+  // the steady loop loaded five ahead and the prologue covers N = 0.
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+  __syncthreads();
+  for (int u = N; u < nsub; ++u) {
+    const uint16_t* K = slot_rt(u % kRing);
+    f32x16 sv, dp;
+    sdp(K, sv, dp);
+    const int rel = (int)(r - (int64_t)u * kSB);  // keys past this row are masked
+    float ds[16];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      float p = fast_exp2(sv[v] * C - lse2);
+      if (8 * (v / 4) + 4 * g + (v % 4) > rel) p = 0.f;
+      ds[v] = p * dp[v];
+    }
+    bf16x8 dsb[2];
+    dsb[0] = pack_bf16x8(ds[0], ds[1], ds[2], ds[3], ds[4], ds[5], ds[6], ds[7]);
+    dsb[1] = pack_bf16x8(ds[8], ds[9], ds[10], ds[11], ds[12], ds[13], ds[14], ds[15]);
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+#pragma unroll
+      for (int db = 0; db < ND; ++db) dq[db] = mfma32(tr_rd(K, hh, db), dsb[hh], dq[db]);
+    }
+  }
+
+  if (rvalid) {
+    uint16_t* qrow = static_cast<uint16_t*>(a.dq) + ((b * s + (r - c0)) * a.Hq + h) * D;
+#pragma unroll
+    for (int db = 0; db < ND; ++db) {
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        *reinterpret_cast<u32x2*>(qrow + 32 * db + 8 * q4 + 4 * g) =
+            pack_bf16x4(dq[db][4 * q4 + 0] * a.scale, dq[db][4 * q4 + 1] * a.scale,
+                        dq[db][4 * q4 + 2] * a.scale, dq[db][4 * q4 + 3] * a.scale);
+      }
+    }
+  }
+}
+
 // Workgroups of the persistent dK/dV kernel that one CU holds at once (its
 // registers allow one; asked of the runtime once).
 int dkdv_groups_per_cu() {
@@ -469,6 +725,12 @@ int dkdv_groups_per_cu() {
 hipError_t launch_bwd_dkdv_mfma32(const ChunkArgs& a, int64_t tiles, hipStream_t stream) {
   const int64_t slots = (int64_t)a.n_cu * dkdv_groups_per_cu();
   hipLaunchKernelGGL(bwd_dkdv_mfma32_kernel, dim3((unsigned)(tiles < slots ? tiles : slots)), dim3(256), 0, stream, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_bwd_dq_mfma32(const ChunkArgs& a, hipStream_t stream) {
+  const dim3 grid((unsigned)((a.c1 - a.c0 + kDqRows - 1) / kDqRows), (unsigned)a.Hq, (unsigned)a.B);
+  hipLaunchKernelGGL(bwd_dq_mfma32_kernel, grid, dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 

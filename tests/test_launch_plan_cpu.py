@@ -87,10 +87,11 @@ def kernels(p):
 
 
 @pytest.mark.parametrize("heads", ["4 4", "8 2", "16 4", "32 8", "32 32"])
-def test_wide_dkdv_by_head_size(plan, heads):
-    """Wide dK/dV launches take the 32x32x16 kernel at head size 128 and the
-    16x16x32 one at 64, whatever the grid."""
-    for c0, c1 in ((0, 20000), (16300, 19059), (122880, 131072)):
-        for D, name in ((128, "bwd_dkdv_mfma32_kernel"), (64, "bwd_dkdv_bf16_kernel")):
-            p, = plan([f"dkdv bf16 1 {heads} {D} {c1} {c0} {c1}"])
-            assert legal(p) and name in kernels(p)[0] and p[0]["grid"][0] <= 256
+def test_wide_backward_by_head_size(plan, heads):
+    """Wide dK/dV and dQ launches take the 32x32x16 kernels at head size 128 and
+    the 16x16x32 ones at 64, whatever the grid."""
+    for c0, c1 in ((0, 20000), (10000, 20000), (114688, 131072)):
+        for D, kind in ((128, "mfma32"), (64, "bf16")):
+            dkdv, dq = plan([f"{op} bf16 1 {heads} {D} {c1} {c0} {c1}" for op in ("dkdv", "dq")])
+            assert legal(dkdv) and f"bwd_dkdv_{kind}_kernel" in kernels(dkdv)[0] and dkdv[0]["grid"][0] <= 256
+            assert legal(dq) and f"bwd_dq_{kind}_kernel" in kernels(dq)[0]
