@@ -1226,20 +1226,49 @@ static int dkdv_groups_per_cu() {
   return n;
 }
 
-// Which dK/dV kernel: 0 the persistent one, 1 split with 32 keys a workgroup, 2
-// split with 64.
-// The split kernels where their workgroups all run at once (one a CU): 32
-// keys times four parts, then 64 times two (D = 64: 64 times four).  Measured
-// (us, this kernel -> split, event times): 4 heads, rows [1536, 2048) 32 -> 17
-// (256 workgroups of 32 keys); 8 heads, rows [1024, 2048) 47 -> 38 (256 of 64);
-// GQA 16/4, rows [3072, 4096) 127 -> 115; D = 64, GQA 32/8, 2048 rows 145 ->
-// 113; but 4 heads, rows [7168, 8192) 67 -> 70 (512 of 64), D = 64, 8/2 x
-// batch 2, rows [3334, 5001) 126 -> 153 (316).  The line is drawn by the whole
-// chunk's keys, so that launches over parts of [0, c1) give what one launch
-// gives.
-static int dkdv_split_mode(const ChunkArgs& a) {
+// Which kernels a chunk's backward takes.  Drawn by the whole chunk's rows and
+// keys, so that launches over parts of [0, c1), and one launch for both
+// gradients or two, give the same results.
+struct SplitPlan {
+  int dkdv;   // 0 the wide kernel, 1 split with 32 keys a workgroup, 2 split with 64
+  bool dq;    // the split kernel
+  bool pair;  // both in one launch, if dQ overwrites nothing that dK/dV reads
+};
+
+// dK/dV: the split kernels where their workgroups all run at once (one a CU):
+// 32 keys times four parts, then 64 times two (D = 64: 64 times four).
+// Measured (us, wide kernel -> split, event times): 4 heads, rows [1536, 2048)
+// 32 -> 17 (256 workgroups of 32 keys); 8 heads, rows [1024, 2048) 47 -> 38
+// (256 of 64); D = 64, GQA 32/8, 2048 rows 145 -> 113; but 4 heads, rows [7168,
+// 8192) 67 -> 70 (512 of 64), D = 64, 8/2 x batch 2, rows [3334, 5001) 126 ->
+// 153 (316).  Two parts halve a workgroup's chain of sub-blocks, which makes
+// up for the unpipelined step only while the chain is short: with more than
+// 4096 query rows to a key 64 times two is the slower on its own (whole
+// backward, wide -> split: 8/2 heads, rows [6656, 8192) 252 -> 263, [4096,
+// 8192) 543 -> 599; 16/4, rows [1024, 4096) 397 -> 427 as 8/2 x 2; at 4400 rows
+// even), but not in one launch with dQ (rows [3500, 4800) 199 -> 151).
+// dQ: the split kernel where its workgroups (64 rows; one a CU by LDS at D =
+// 128, two at D = 64) all run at once.  Measured (us, wide -> split): 4 heads,
+// rows [1536, 2048) 45 -> 29 (32 workgroups); GQA 16/4, rows [3072, 4096) 80 ->
+// 53 (256); but 32 heads, 1024 rows 30 -> 34 (512); D = 64, 8 heads x batch 2,
+// rows [3334, 5001) 67 -> 61 (432).
+// Both in one launch if both take the split kernels and their workgroups are
+// at most two to a place on the card (us, pre + dK/dV + dQ, one after the other
+// -> pair): 4 heads, rows [0, 512) 27.9 -> 16.5, [1536, 2048) 43.3 -> 28.6 (320
+// workgroups on 256 CUs); 8 heads, rows [1024, 2048) 64.1 -> 53.9 (512); D = 64,
+// 8/2 x batch 2, rows [1667, 3334) 138 -> 115; but GQA 16/4, rows [3072, 4096)
+// 166 -> 183 and 8/2, rows [2048, 4096) 182 -> 192 (768).
+static SplitPlan split_plan(const ChunkArgs& a) {
+  const bool d64 = a.D == 64;
+  const int64_t s = a.c1 - a.c0, heads = a.Hq * a.B, n_cu = a.n_cu;
   const int64_t k64 = (a.c1 + 63) / 64 * a.Hkv * a.B, k32 = (a.c1 + 31) / 32 * a.Hkv * a.B;
-  return a.D == 128 && k32 <= a.n_cu ? 1 : k64 <= a.n_cu ? 2 : 0;
+  const int64_t q64 = (s + 63) / 64 * heads, q32 = (s + 31) / 32 * heads;
+  const int mode = !d64 && k32 <= n_cu ? 1 : k64 <= n_cu ? 2 : 0;
+  SplitPlan p;
+  p.dq = q64 <= n_cu * (d64 ? 2 : 1);
+  p.pair = mode && p.dq && (d64 ? q64 : q32) + (mode == 1 ? k32 : k64) <= n_cu * (d64 ? 4 : 2);
+  p.dkdv = d64 || mode == 1 || p.pair || a.Hq / a.Hkv * s <= 4096 ? mode : 0;
+  return p;
 }
 
 hipError_t launch_bwd_dkdv_bf16(const ChunkArgs& a, hipStream_t stream) {
@@ -1247,7 +1276,7 @@ hipError_t launch_bwd_dkdv_bf16(const ChunkArgs& a, hipStream_t stream) {
   if (a.D != 128 && a.D != 64) return hipErrorInvalidValue;
   const int64_t tiles = (a.kv1 - a.kv0 + kKvKeys - 1) / kKvKeys * a.Hkv * a.B;
   if (tiles > 0x7fffffff) return hipErrorInvalidValue;
-  const int mode = dkdv_split_mode(a);
+  const int mode = split_plan(a).dkdv;
   if (mode) {
     const int r = mode == 2 ? 64 : 32;
     const dim3 grid((unsigned)((a.kv1 - a.kv0 + r - 1) / r), (unsigned)a.Hkv, (unsigned)a.B);
@@ -1263,20 +1292,10 @@ hipError_t launch_bwd_dkdv_bf16(const ChunkArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// The split kernel where its workgroups (64 rows; one a CU by LDS at D = 128,
-// two at D = 64) all run at once.  Measured (us, this kernel -> split, event
-// times): 4 heads, rows [1536, 2048) 45 -> 29 (32 workgroups); GQA 16/4, rows
-// [3072, 4096) 80 -> 53 (256); but 32 heads, 1024 rows 30 -> 34 (512); D = 64,
-// 8 heads x batch 2, rows [3334, 5001) 67 -> 61 (432), 16 heads, rows [6000,
-// 8000) 102 -> 100 (512).
-static bool dq_split(const ChunkArgs& a) {
-  return (a.c1 - a.c0 + 63) / 64 * a.Hq * a.B <= (int64_t)a.n_cu * (a.D == 64 ? 2 : 1);
-}
-
 hipError_t launch_bwd_dq_bf16(const ChunkArgs& a, hipStream_t stream) {
   if (a.D != 128 && a.D != 64) return hipErrorInvalidValue;
   const int64_t s = a.c1 - a.c0;
-  if (dq_split(a)) {
+  if (split_plan(a).dq) {
     const dim3 grid((unsigned)((s + 63) / 64), (unsigned)a.Hq, (unsigned)a.B);
     if (a.D == 128) hipLaunchKernelGGL(bwd_dq_split_kernel<128>, grid, dim3(512), 0, stream, a);
     else hipLaunchKernelGGL(bwd_dq_split_kernel<64>, grid, dim3(512), 0, stream, a);
@@ -1289,38 +1308,22 @@ hipError_t launch_bwd_dq_bf16(const ChunkArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// The workgroups of both kinds of a chunk's split backward as one launch, if
-// both take the split kernels, they are at most two to a place on the card, and
-// dQ overwrites nothing the dK/dV reads.  Measured (us, pre + dK/dV + dQ, one
-// after the other -> pair): 4 heads, rows [0, 512) 27.9 -> 16.5, [1536, 2048)
-// 43.3 -> 28.6 (320 workgroups on 256 CUs); 8 heads, rows [1024, 2048) 64.1 ->
-// 53.9 (512); D = 64, 8/2 x batch 2, rows [1667, 3334) 138 -> 115; but GQA 16/4,
-// rows [3072, 4096) 166 -> 183 and 8/2, rows [2048, 4096) 182 -> 192 (768).
-static bool pair_grid(const ChunkArgs& a, PairGrid* p) {
-  const int mode = dkdv_split_mode(a);
-  if ((a.D != 128 && a.D != 64) || !mode || !dq_split(a)) return false;
-  const int64_t s = a.c1 - a.c0, rows = a.D == 64 ? 64 : 32, keys = mode == 2 ? 64 : 32;
-  const int64_t dqx = (s + rows - 1) / rows, dkdvx = (a.kv1 - a.kv0 + keys - 1) / keys;
-  const int64_t ndq = dqx * a.Hq * a.B, ndkdv = dkdvx * a.Hkv * a.B;
-  if (ndq + ndkdv > (int64_t)a.n_cu * (a.D == 64 ? 4 : 2)) return false;
-  if (dq_overwrites_inputs(a, 2)) return false;
-  const int64_t parts = a.D == 128 && mode == 2 ? 2 : 4;
-  const int dq_first = a.c1 / kDqParts >= a.Hq / a.Hkv * s / parts;
-  *p = PairGrid{dq_first, (int)ndq, (int)dqx, (int)ndkdv, (int)dkdvx};
-  return true;
-}
-
 bool bwd_pair_bf16(const ChunkArgs& a) {
-  PairGrid p;
-  return pair_grid(a, &p);
+  return (a.D == 128 || a.D == 64) && split_plan(a).pair && !dq_overwrites_inputs(a, 2);
 }
 
 hipError_t launch_bwd_pair_bf16(const ChunkArgs& a, hipStream_t stream) {
-  PairGrid p;
-  if (a.kv0 < 0 || a.kv1 > a.c1 || a.kv0 >= a.kv1 || !pair_grid(a, &p)) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)(p.ndq + p.ndkdv));
+  if (a.kv0 < 0 || a.kv1 > a.c1 || a.kv0 >= a.kv1 || !bwd_pair_bf16(a)) return hipErrorInvalidValue;
+  const int mode = split_plan(a).dkdv;
+  const int64_t s = a.c1 - a.c0, rows = a.D == 64 ? 64 : 32, keys = mode == 2 ? 64 : 32;
+  const int64_t dqx = (s + rows - 1) / rows, dkdvx = (a.kv1 - a.kv0 + keys - 1) / keys;
+  const int64_t ndq = dqx * a.Hq * a.B, ndkdv = dkdvx * a.Hkv * a.B;
+  const int64_t parts = a.D == 128 && mode == 2 ? 2 : 4;
+  const int dq_first = a.c1 / kDqParts >= a.Hq / a.Hkv * s / parts;
+  const PairGrid p{dq_first, (int)ndq, (int)dqx, (int)ndkdv, (int)dkdvx};
+  const dim3 grid((unsigned)(ndq + ndkdv));
   if (a.D == 64) hipLaunchKernelGGL((bwd_pair_kernel<64, 2, 4>), grid, dim3(512), 0, stream, a, p);
-  else if (dkdv_split_mode(a) == 1) hipLaunchKernelGGL((bwd_pair_kernel<128, 1, 4>), grid, dim3(256), 0, stream, a, p);
+  else if (mode == 1) hipLaunchKernelGGL((bwd_pair_kernel<128, 1, 4>), grid, dim3(256), 0, stream, a, p);
   else hipLaunchKernelGGL((bwd_pair_kernel<128, 2, 2>), grid, dim3(256), 0, stream, a, p);
   return hipGetLastError();
 }

@@ -95,3 +95,26 @@ def test_wide_backward_by_head_size(plan, heads):
             dkdv, dq = plan([f"{op} bf16 1 {heads} {D} {c1} {c0} {c1}" for op in ("dkdv", "dq")])
             assert legal(dkdv) and f"bwd_dkdv_{kind}_kernel" in kernels(dkdv)[0] and dkdv[0]["grid"][0] <= 256
             assert legal(dq) and f"bwd_dq_{kind}_kernel" in kernels(dq)[0]
+
+
+# 256 compute units.  Rows [c0, c1) of heads Hq/Hkv: the kernels of dK/dV, dQ and the pair ("none": separate launches).
+@pytest.mark.parametrize("B,Hq,Hkv,D,c0,c1,dkdv,dq,pair", [
+    (1, 4, 4, 128, 1536, 2048, "dkdv_split_kernelILi128ELi1ELi4E", "dq_split", "pair_kernelILi128ELi1ELi4E"),
+    (1, 8, 8, 128, 1024, 2048, "dkdv_split_kernelILi128ELi2ELi2E", "dq_split", "pair_kernelILi128ELi2ELi2E"),
+    (1, 16, 4, 128, 3072, 4096, "dkdv_split_kernelILi128ELi2ELi2E", "dq_split", "none"),  # 4096 query rows to a key
+    (1, 16, 4, 128, 3071, 4096, "dkdv_mfma32", "dq_mfma32", "none"),  # 4100
+    (1, 8, 2, 128, 6144, 8192, "dkdv_mfma32", "dq_split", "none"),
+    (1, 8, 2, 128, 3500, 4800, "dkdv_split_kernelILi128ELi2ELi2E", "dq_split", "pair_kernelILi128ELi2ELi2E"),  # 5200
+    (1, 8, 2, 128, 0, 7680, "dkdv_mfma32", "dq_mfma32", "none"),
+    (1, 1, 1, 128, 2000, 10192, "dkdv_split_kernelILi128ELi2ELi2E", "dq_split", "pair_kernelILi128ELi2ELi2E"),
+    (1, 32, 8, 64, 0, 1024, "dkdv_split_kernelILi64ELi2ELi4E", "dq_split", "pair_kernelILi64ELi2ELi4E"),
+])
+def test_backward_kernels_of_small_grids(plan, B, Hq, Hkv, D, c0, c1, dkdv, dq, pair):
+    args = f"bf16 {B} {Hq} {Hkv} {D} {c1} {c0} {c1}"
+    got = plan([f"{op} {args}" for op in ("dkdv", "dq", "pair")])
+    for p, want in zip(got, (dkdv, dq, pair)):
+        assert (p == "none") if want == "none" else (legal(p) and want in kernels(p)[0]), (p, want)
+    mid = c1 // 2 + 13  # a part of the keys: the same kernel
+    for lo, hi in ((0, mid), (mid, c1)):
+        part, = plan([f"dkdv {args} {lo} {hi}"])
+        assert kernels(part) == kernels(got[0])
