@@ -29,12 +29,13 @@
 // a time, outside the pipeline.  Grids too small for the chip take the split
 // kernels further down.
 //
-// The products here are 16x16x32 MFMAs; the wide kernels of head size 128 are
-// in attn_bwd_bf16_mfma32.hip on 32x32x16.  Both occupy the matrix pipe for as
-// many cycles a step.  The smaller form takes less energy, so the clock rises,
-// but the lone wave on each SIMD issues twice the MFMAs: at D = 64, with half
-// the MFMAs per exponential, that gains (dK/dV 1-3%, dQ up to 5%), at 128 it
-// loses.  What is left is the one wave's instruction stream: moving half the
+// The products here are 16x16x32 MFMAs; the wide kernels of head size 128, and
+// dQ of 64 with one workgroup on most CUs, are in attn_bwd_bf16_mfma32.hip on
+// 32x32x16.  Both occupy the matrix pipe for as many cycles a step.  The
+// smaller form takes less energy, so the clock rises, but a wave alone on its
+// SIMD issues twice the MFMAs: at D = 64, with half the MFMAs per exponential,
+// that gains (dK/dV 1-5%, dQ over several passes up to 5%), at 128 it loses.
+// What is left is the one wave's instruction stream: moving half the
 // exponentials from the S/dP phase to the gradient phase changed nothing.
 #include "bwd_tiles.h"
 #include "sppo_kernels.h"
@@ -1292,14 +1293,18 @@ hipError_t launch_bwd_dkdv_bf16(const ChunkArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// The wide kernel of D = 64: 32x32x16 while most CUs hold one workgroup of 128
+// rows, 16x16x32 where two overlap on most (figures beside the former: 4 heads,
+// rows [10000, 20000), a load of 0.93, 311 / 323 us; 16 heads, rows [8192,
+// 12288), 1.67, 253 / 249).
 hipError_t launch_bwd_dq_bf16(const ChunkArgs& a, hipStream_t stream) {
   if (a.D != 128 && a.D != 64) return hipErrorInvalidValue;
-  const int64_t s = a.c1 - a.c0;
+  const int64_t s = a.c1 - a.c0, wide = (s + kDqRows - 1) / kDqRows * a.Hq * a.B;
   if (split_plan(a).dq) {
     const dim3 grid((unsigned)((s + 63) / 64), (unsigned)a.Hq, (unsigned)a.B);
     if (a.D == 128) hipLaunchKernelGGL(bwd_dq_split_kernel<128>, grid, dim3(512), 0, stream, a);
     else hipLaunchKernelGGL(bwd_dq_split_kernel<64>, grid, dim3(512), 0, stream, a);
-  } else if (a.D == 128) {
+  } else if (a.D == 128 || wide <= a.n_cu || load_per_cu(wide, a.c0, a.c1, a.n_cu) < 0.95) {
     return launch_bwd_dq_mfma32(a, stream);
   } else {
     const dim3 grid((unsigned)((s + kDqRows - 1) / kDqRows), (unsigned)a.Hq, (unsigned)a.B);

@@ -1,21 +1,25 @@
-// The wide kernels of the bf16 backward for head size 128, dK/dV and dQ, on
-// 32x32x16 MFMAs; the work, the LDS ring and the pipeline are those of the
-// 16x16x32 kernels of attn_bwd_bf16.hip.
+// Wide kernels of the bf16 backward on 32x32x16 MFMAs: dK/dV and dQ of head
+// size 128, and dQ of 64 where most compute units hold one workgroup.  The
+// work, the LDS ring and the pipeline are those of the 16x16x32 kernels of
+// attn_bwd_bf16.hip.
 //
-// Why the larger MFMA here: with one wave per SIMD the kernels are bound by
-// that wave's instruction stream, and 16x16x32 issues twice the MFMAs.
-// Measured in turn with 16x16x32 forms on three machines (us, 32x32x16 /
-// 16x16x32):
+// Why the larger MFMA: with one wave per SIMD the kernels are bound by that
+// wave's instruction stream, and 16x16x32 issues twice the MFMAs.  Measured in
+// turn with 16x16x32 forms on three machines (us, 32x32x16 / 16x16x32):
 //   dK/dV  4 heads, 6000 rows 158 / 172; 8/2 heads, rows [16300, 19059) 549 /
 //          577; 16/4 heads, rows [4096, 8192) 403 / 424; 32 heads, rows [28672,
 //          32768) 3540 / 3708, [57344, 65536) 13901 / 14435, [122880, 131072)
 //          28340 / 28742; the other way by 2% in a few (8 heads, rows [10000,
-//          20000) 1034 / 1016)
+//          20000) 1034 / 1016).  D = 64 is 1-5% faster with 16x16x32 in every
+//          grid.
 //   dQ     4 heads, 6000 rows 100 / 112; 8/2 heads, rows [16300, 19059) 304 /
 //          335; 32 heads, 2048 rows 73 / 78, rows [2048, 4096) 158 / 161; in
 //          larger grids between 4% less and 4% more, machine to machine (32
-//          heads, rows [122880, 131072) 20.43 / 21.26 ms, 20.76 / 19.98)
-// At head size 64 the smaller form is 1-3% the faster.
+//          heads, rows [122880, 131072) 20.43 / 21.26 ms, 20.76 / 19.98).  D =
+//          64: 1 head, rows [7000, 24408) 261 / 274; 4 heads, rows [12000,
+//          18144) 198 / 206; 16 heads, rows [7000, 8088) 90.7 / 95.4; but two
+//          workgroups a CU overlap: 32/8 heads, rows [4096, 8192) 289 / 280, 32
+//          heads, rows [8192, 16384) 1062 / 1010.
 #include "bwd_tiles.h"
 #include "mfma32.h"
 #include "sppo_kernels.h"
@@ -25,8 +29,9 @@ namespace {
 
 // ------------------------------------------------------------------ dK dV
 __global__ __launch_bounds__(256, 1) void bwd_dkdv_mfma32_kernel(ChunkArgs a) {
-  using T = Tile32;
-  constexpr int D = T::D, P = T::P, NK = D / 16, ND = D / 32;
+  constexpr int D = 128;
+  using T = Tile32<D>;
+  constexpr int P = T::P, NK = D / 16, ND = D / 32;
   constexpr int IPWQ = (kSB / T::RPI) / 4;  // DMA instructions per wave per tensor per sub-block
   static_assert(IPWQ >= 1 && IPWQ * 4 * T::RPI == kSB, "sub-block splits over 4 waves");
   constexpr int DMA_PER_SB = 2 * IPWQ + 1;  // Q, dO, and one for the [LSE2 | -Delta] record
@@ -457,9 +462,10 @@ __global__ __launch_bounds__(256, 1) void bwd_dkdv_mfma32_kernel(ChunkArgs a) {
 }
 
 // --------------------------------------------------------------------- dQ
+template <int D>
 __global__ __launch_bounds__(256, 1) void bwd_dq_mfma32_kernel(ChunkArgs a) {
-  using T = Tile32;
-  constexpr int D = T::D, P = T::P, NK = D / 16, ND = D / 32;
+  using T = Tile32<D>;
+  constexpr int P = T::P, NK = D / 16, ND = D / 32;
   constexpr int IPWK = (kSB / T::RPI) / 4;  // DMA instructions per wave per tensor per sub-block
   static_assert(IPWK >= 1 && IPWK * 4 * T::RPI == kSB, "sub-block splits over 4 waves");
   constexpr int DMA_PER_SB = 2 * IPWK;
@@ -730,7 +736,8 @@ hipError_t launch_bwd_dkdv_mfma32(const ChunkArgs& a, int64_t tiles, hipStream_t
 
 hipError_t launch_bwd_dq_mfma32(const ChunkArgs& a, hipStream_t stream) {
   const dim3 grid((unsigned)((a.c1 - a.c0 + kDqRows - 1) / kDqRows), (unsigned)a.Hq, (unsigned)a.B);
-  hipLaunchKernelGGL(bwd_dq_mfma32_kernel, grid, dim3(256), 0, stream, a);
+  if (a.D == 128) hipLaunchKernelGGL(bwd_dq_mfma32_kernel<128>, grid, dim3(256), 0, stream, a);
+  else hipLaunchKernelGGL(bwd_dq_mfma32_kernel<64>, grid, dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 

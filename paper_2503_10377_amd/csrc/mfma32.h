@@ -1,6 +1,6 @@
-// What the 32x32x16 attention kernels (head size 128) use beside
-// tile_common.h: the MFMA wrapper and the LDS tile layout that its operands
-// read without bank conflicts.
+// What the 32x32x16 attention kernels use beside tile_common.h: the MFMA
+// wrapper and the LDS tile layout that its operands read without bank
+// conflicts.
 //
 // MFMA register layout (v_mfma_f32_32x32x16_bf16, wave64):
 //   A[i][k] : lane l holds row i = l%32 and 8 k-values in "k-slots"
@@ -23,17 +23,22 @@ __device__ __forceinline__ f32x16 mfma32(const bf16x8& a, const bf16x8& b, const
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
-// A bf16 tile [rows][128], unpadded, the 16-byte chunk c of row r at physical
-// chunk c ^ f(r): 16 consecutive rows at one chunk (natural reads) hit 16
-// different slots of the 256-byte bank window, and the 4 rows x 4 chunks of 32
-// lanes of a transposed read four different 64-byte quarters.
+// A bf16 tile [rows][D], unpadded, the 16-byte chunk c of row r at physical
+// chunk c ^ f(r): natural reads (16 consecutive rows at one chunk) hit 16
+// different slots of the 256-byte bank window (D = 64: two rows a window, f
+// bijective per row parity), and the 4 rows x 4 chunks of 32 lanes of a
+// transposed read four different 64-byte quarters.
+template <int D>
 struct Tile32 {
-  static constexpr int D = 128;
   static constexpr int P = D;         // row pitch, elements
   static constexpr int CG = D / 8;    // 16-byte chunks per row
   static constexpr int RPI = 512 / D; // rows per LDS-DMA wave instruction
   static __device__ __forceinline__ int f(int r) {
-    return ((r & 3) << 2) | ((r >> 2) & 3);
+    if constexpr (D == 128) {
+      return ((r & 3) << 2) | ((r >> 2) & 3);
+    } else {
+      return (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
+    }
   }
   // Natural operand read of k-step kk for rows rb + l%32 (rb % 32 == 0):
   // element offset (add rb * P).

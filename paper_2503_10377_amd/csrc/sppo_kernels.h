@@ -61,8 +61,7 @@ hipError_t launch_bwd_dkdv_bf16(const ChunkArgs& a, hipStream_t stream);
 hipError_t launch_bwd_dq_bf16(const ChunkArgs& a, hipStream_t stream);
 bool bwd_pair_bf16(const ChunkArgs& a);
 hipError_t launch_bwd_pair_bf16(const ChunkArgs& a, hipStream_t stream);
-// The wide kernels of head size 128 on 32x32x16 MFMAs, where the launchers
-// above take them.
+// Wide kernels on 32x32x16 MFMAs, where the launchers above take them.
 hipError_t launch_bwd_dkdv_mfma32(const ChunkArgs& a, int64_t tiles, hipStream_t stream);
 hipError_t launch_bwd_dq_mfma32(const ChunkArgs& a, hipStream_t stream);
 hipError_t launch_fwd_f32(const ChunkArgs& a, hipStream_t stream);
@@ -71,6 +70,14 @@ hipError_t launch_bwd_dkdv_f32(const ChunkArgs& a, hipStream_t stream);
 hipError_t launch_bwd_dq_f32(const ChunkArgs& a, hipStream_t stream);
 bool bwd_pair_f32(const ChunkArgs& a);
 hipError_t launch_bwd_pair_f32(const ChunkArgs& a, hipStream_t stream);
+
+// Work of a launch of `groups` workgroups over query tiles of rows [c0, c1),
+// longest first, as a share of every compute unit busy for the longest (a
+// tile's work is its keys, from c0 to c1): below 1, most units hold one
+// workgroup for most of the launch.
+inline double load_per_cu(int64_t groups, int64_t c0, int64_t c1, int n_cu) {
+  return (double)groups * (double)(c0 + c1) / (2.0 * n_cu * (double)c1);
+}
 
 // Whether dQ shares memory with what the dK/dV kernels read (elements of elt
 // bytes): a caller may let dQ replace Q or dO, which holds only while dQ runs

@@ -88,9 +88,9 @@ def kernels(p):
 
 @pytest.mark.parametrize("heads", ["4 4", "8 2", "16 4", "32 8", "32 32"])
 def test_wide_backward_by_head_size(plan, heads):
-    """Wide dK/dV and dQ launches take the 32x32x16 kernels at head size 128 and
-    the 16x16x32 ones at 64, whatever the grid."""
-    for c0, c1 in ((0, 20000), (10000, 20000), (114688, 131072)):
+    """Wide dK/dV and dQ launches of several passes take the 32x32x16 kernels at
+    head size 128 and the 16x16x32 ones at 64."""
+    for c0, c1 in ((0, 30000), (10000, 26000), (114688, 131072)):
         for D, kind in ((128, "mfma32"), (64, "bf16")):
             dkdv, dq = plan([f"{op} bf16 1 {heads} {D} {c1} {c0} {c1}" for op in ("dkdv", "dq")])
             assert legal(dkdv) and f"bwd_dkdv_{kind}_kernel" in kernels(dkdv)[0] and dkdv[0]["grid"][0] <= 256
@@ -118,3 +118,13 @@ def test_backward_kernels_of_small_grids(plan, B, Hq, Hkv, D, c0, c1, dkdv, dq, 
     for lo, hi in ((0, mid), (mid, c1)):
         part, = plan([f"dkdv {args} {lo} {hi}"])
         assert kernels(part) == kernels(got[0])
+
+
+@pytest.mark.parametrize("Hq,c0,c1,one", [(1, 0, 33000, True), (1, 7000, 41000, True), (1, 46000, 80000, True),
+                                          (4, 10000, 20000, True), (8, 0, 4097, True), (8, 0, 6000, True), (12, 2000, 4730, True),
+                                          (12, 8000, 11000, False), (32, 4096, 8192, False), (8, 0, 8192, False)])
+def test_wide_dq_of_head_size_64_by_load(plan, Hq, c0, c1, one):
+    """The 32x32x16 kernel while most compute units hold one workgroup (no more
+    workgroups of 128 rows than 256, or short tiles among them)."""
+    p, = plan([f"dq bf16 1 {Hq} {Hq} 64 {c1} {c0} {c1}"])
+    assert legal(p) and ("bwd_dq_mfma32_kernelILi64E" if one else "bwd_dq_bf16_kernel") in kernels(p)[0]
