@@ -1246,13 +1246,19 @@ struct SplitPlan {
 // up for the unpipelined step only while the chain is short: with more than
 // 4096 query rows to a key 64 times two is the slower on its own (whole
 // backward, wide -> split: 8/2 heads, rows [6656, 8192) 252 -> 263, [4096,
-// 8192) 543 -> 599; 16/4, rows [1024, 4096) 397 -> 427 as 8/2 x 2; at 4400 rows
+// 8192) 543 -> 599; 16/4 heads, rows [1024, 4096) 394 -> 427; at 4400 rows
 // even), but not in one launch with dQ (rows [3500, 4800) 199 -> 151).
-// dQ: the split kernel where its workgroups (64 rows; one a CU by LDS at D =
-// 128, two at D = 64) all run at once.  Measured (us, wide -> split): 4 heads,
-// rows [1536, 2048) 45 -> 29 (32 workgroups); GQA 16/4, rows [3072, 4096) 80 ->
-// 53 (256); but 32 heads, 1024 rows 30 -> 34 (512); D = 64, 8 heads x batch 2,
-// rows [3334, 5001) 67 -> 61 (432).
+// dQ: the split kernel where its workgroups (64 rows) all run at once, one a
+// CU.  Measured (us, wide -> split): 4 heads, rows [1536, 2048) 45 -> 29 (32
+// workgroups); GQA 16/4, rows [3072, 4096) 80 -> 53 (256); but 32 heads, 1024
+// rows 30 -> 34 (512).  D = 64 has room for two a CU: twice the wide kernel's
+// workgroups then stream the keys, which pays while an XCD has one head and up
+// to 12288 keys of it (3 MiB of K and V in its L2) or two heads and 4096: 8
+// heads, rows [2000, 6096) 76 -> 64 (512 workgroups), [7000, 11096) 137 -> 125,
+// 16 heads, rows [2000, 3536) 46 -> 44 (384); but 8 heads, rows [12000, 14176)
+// 155 -> 160 (272), 16 heads, rows [7000, 8088) 91 -> 98, 32 heads, rows [14000,
+// 14768) 163 -> 189 (384), 64/8 heads, 448 rows 12 -> 15.5 (512).  With the pair
+// it always does.
 // Both in one launch if both take the split kernels and their workgroups are
 // at most two to a place on the card (us, pre + dK/dV + dQ, one after the other
 // -> pair): 4 heads, rows [0, 512) 27.9 -> 16.5, [1536, 2048) 43.3 -> 28.6 (320
@@ -1266,8 +1272,10 @@ static SplitPlan split_plan(const ChunkArgs& a) {
   const int64_t q64 = (s + 63) / 64 * heads, q32 = (s + 31) / 32 * heads;
   const int mode = !d64 && k32 <= n_cu ? 1 : k64 <= n_cu ? 2 : 0;
   SplitPlan p;
-  p.dq = q64 <= n_cu * (d64 ? 2 : 1);
-  p.pair = mode && p.dq && (d64 ? q64 : q32) + (mode == 1 ? k32 : k64) <= n_cu * (d64 ? 4 : 2);
+  const bool at_once = q64 <= n_cu * (d64 ? 2 : 1);
+  const int64_t heads_xcd = (heads + 7) / 8;
+  p.pair = mode && at_once && (d64 ? q64 : q32) + (mode == 1 ? k32 : k64) <= n_cu * (d64 ? 4 : 2);
+  p.dq = p.pair || q64 <= n_cu || (d64 && at_once && a.c1 <= (heads_xcd == 1 ? 12288 : heads_xcd == 2 ? 4096 : 0));
   p.dkdv = d64 || mode == 1 || p.pair || a.Hq / a.Hkv * s <= 4096 ? mode : 0;
   return p;
 }

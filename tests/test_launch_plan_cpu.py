@@ -107,6 +107,13 @@ def test_wide_backward_by_head_size(plan, heads):
     (1, 8, 2, 128, 3500, 4800, "dkdv_split_kernelILi128ELi2ELi2E", "dq_split", "pair_kernelILi128ELi2ELi2E"),  # 5200
     (1, 8, 2, 128, 0, 7680, "dkdv_mfma32", "dq_mfma32", "none"),
     (1, 1, 1, 128, 2000, 10192, "dkdv_split_kernelILi128ELi2ELi2E", "dq_split", "pair_kernelILi128ELi2ELi2E"),
+    (1, 16, 16, 64, 3000, 4000, "dkdv_bf16_kernel", "dq_split", "none"),  # 256 workgroups of 64 rows
+    (1, 16, 16, 64, 2560, 4096, "dkdv_bf16_kernel", "dq_split", "none"),  # 384, 2 x 4096 keys an XCD
+    (1, 16, 16, 64, 2561, 4097, "dkdv_bf16_kernel", "dq_mfma32", "none"),
+    (1, 8, 8, 64, 8192, 12288, "dkdv_bf16_kernel", "dq_split", "none"),
+    (1, 8, 8, 64, 10000, 12289, "dkdv_bf16_kernel", "dq_mfma32", "none"),
+    (1, 17, 17, 64, 1000, 2000, "dkdv_bf16_kernel", "dq_mfma32", "none"),  # 3 heads an XCD
+    (2, 32, 8, 64, 1000, 1500, "dkdv_bf16_kernel", "dq_mfma32", "none"),
     (1, 32, 8, 64, 0, 1024, "dkdv_split_kernelILi64ELi2ELi4E", "dq_split", "pair_kernelILi64ELi2ELi4E"),
 ])
 def test_backward_kernels_of_small_grids(plan, B, Hq, Hkv, D, c0, c1, dkdv, dq, pair):
@@ -120,7 +127,7 @@ def test_backward_kernels_of_small_grids(plan, B, Hq, Hkv, D, c0, c1, dkdv, dq, 
         assert kernels(part) == kernels(got[0])
 
 
-@pytest.mark.parametrize("Hq,c0,c1,one", [(1, 0, 33000, True), (1, 7000, 41000, True), (1, 46000, 80000, True),
+@pytest.mark.parametrize("Hq,c0,c1,one", [(1, 0, 32768, True), (1, 7000, 24408, True), (1, 7000, 41000, True), (1, 46000, 80000, True),
                                           (4, 10000, 20000, True), (8, 0, 4097, True), (8, 0, 6000, True), (12, 2000, 4730, True),
                                           (12, 8000, 11000, False), (32, 4096, 8192, False), (8, 0, 8192, False)])
 def test_wide_dq_of_head_size_64_by_load(plan, Hq, c0, c1, one):
