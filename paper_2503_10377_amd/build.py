@@ -37,6 +37,7 @@ EXTRA = {
     "gemm_bf16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "attn_fwd_bf16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "attn_bwd_bf16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "attn_fwd_bf16_mfma32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "attn_bwd_bf16_mfma32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
 }
 

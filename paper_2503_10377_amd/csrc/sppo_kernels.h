@@ -62,6 +62,7 @@ hipError_t launch_bwd_dq_bf16(const ChunkArgs& a, hipStream_t stream);
 bool bwd_pair_bf16(const ChunkArgs& a);
 hipError_t launch_bwd_pair_bf16(const ChunkArgs& a, hipStream_t stream);
 // Wide kernels on 32x32x16 MFMAs, where the launchers above take them.
+hipError_t launch_fwd_mfma32(const ChunkArgs& a, hipStream_t stream);
 hipError_t launch_bwd_dkdv_mfma32(const ChunkArgs& a, int64_t tiles, hipStream_t stream);
 hipError_t launch_bwd_dq_mfma32(const ChunkArgs& a, hipStream_t stream);
 hipError_t launch_fwd_f32(const ChunkArgs& a, hipStream_t stream);

@@ -135,3 +135,14 @@ def test_wide_dq_of_head_size_64_by_load(plan, Hq, c0, c1, one):
     workgroups of 128 rows than 256, or short tiles among them)."""
     p, = plan([f"dq bf16 1 {Hq} {Hq} 64 {c1} {c0} {c1}"])
     assert legal(p) and ("bwd_dq_mfma32_kernelILi64E" if one else "bwd_dq_bf16_kernel") in kernels(p)[0]
+
+
+@pytest.mark.parametrize("Hq,D,c0,c1,want", [
+    (4, 128, 0, 4096, "fwd_split"), (4, 128, 0, 4097, "fwd_mfma32"), (4, 128, 6000, 12000, "fwd_mfma32"),
+    (16, 128, 6000, 8048, "fwd_mfma32"), (16, 128, 14000, 16049, "fwd_bf16"),  # 256 workgroups, 272 at a load of 0.99
+    (8, 128, 0, 5376, "fwd_mfma32"), (8, 128, 3000, 8376, "fwd_mfma32"), (8, 128, 12000, 16352, "fwd_bf16"),
+    (32, 128, 0, 2048, "fwd_bf16"), (8, 64, 0, 4096, "fwd_split"), (8, 64, 0, 6000, "fwd_mfma32"),
+    (16, 64, 8192, 12288, "fwd_bf16"), (32, 64, 0, 131072, "fwd_bf16")])
+def test_forward_by_load(plan, Hq, D, c0, c1, want):
+    p, = plan([f"fwd bf16 1 {Hq} {Hq} {D} {c1} {c0} {c1}"])
+    assert legal(p) and want in kernels(p)[0] and f"ILi{D}E" in kernels(p)[0]
