@@ -570,6 +570,9 @@ hipError_t launch_fwd_bf16(const ChunkArgs& a, hipStream_t stream) {
   // two at D = 64) all run at once.  Forward of 2048 rows x 4 heads x 128 (128
   // workgroups) 33 -> 20 us, of 512 x 32 (256) 9 -> 6.5, but of 1024 x 32 (512)
   // 18 -> 24; D = 64: 1667 x 8 x batch 2 (432) 21 -> 17, 2048 x 32 (1024) even.
+  // Up to 64 keys two of its four parts have nothing to do and the sum over
+  // them costs more than it saves (64 rows x 16/4 heads 7.5 -> 9.2 us, 32 x 32
+  // 7.0 -> 8.4; 128 keys 10.3 -> 9.8).
   // The others by the load of their 128-row workgroups on the compute units:
   // 32x32x16 with no more than one a unit, or where the long ones run alone for
   // most of the launch (8 heads, 5376 rows 92 / 97 us against 16x16x32, 336
@@ -577,7 +580,7 @@ hipError_t launch_fwd_bf16(const ChunkArgs& a, hipStream_t stream) {
   // [12000, 16352) 339 / 318, 272 at 0.92).
   const int64_t split = (s + 63) / 64 * a.Hq * a.B, wide = (s + kFwdBR - 1) / kFwdBR * a.Hq * a.B;
   const int cus = device_cus();
-  if (split <= (int64_t)cus * (a.D == 64 ? 2 : 1)) {
+  if (a.c1 > 64 && split <= (int64_t)cus * (a.D == 64 ? 2 : 1)) {
     const dim3 grid((unsigned)((s + 63) / 64), (unsigned)a.Hq, (unsigned)a.B);
     if (a.D == 128) hipLaunchKernelGGL(fwd_split_kernel<128>, grid, dim3(512), 0, stream, a);
     else hipLaunchKernelGGL(fwd_split_kernel<64>, grid, dim3(512), 0, stream, a);

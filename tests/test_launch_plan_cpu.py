@@ -138,6 +138,7 @@ def test_wide_dq_of_head_size_64_by_load(plan, Hq, c0, c1, one):
 
 
 @pytest.mark.parametrize("Hq,D,c0,c1,want", [
+    (2, 128, 0, 64, "fwd_mfma32"), (2, 64, 63, 64, "fwd_mfma32"), (2, 128, 0, 65, "fwd_split"),
     (4, 128, 0, 4096, "fwd_split"), (4, 128, 0, 4097, "fwd_mfma32"), (4, 128, 6000, 12000, "fwd_mfma32"),
     (16, 128, 6000, 8048, "fwd_mfma32"), (16, 128, 14000, 16049, "fwd_bf16"),  # 256 workgroups, 272 at a load of 0.99
     (8, 128, 0, 5376, "fwd_mfma32"), (8, 128, 3000, 8376, "fwd_mfma32"), (8, 128, 12000, 16352, "fwd_bf16"),
