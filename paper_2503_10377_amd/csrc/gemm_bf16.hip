@@ -15,7 +15,8 @@
 // Every product is v_mfma_f32_16x16x32_bf16 with B as its first operand, so
 // the accumulators hold C^T and a lane stores runs of consecutive columns.
 // k-steps are added in order whatever the tile, so the tile size never changes
-// a result's bits.
+// a result's bits (but TN products of up to 16 k-blocks that write C without
+// reading it have a kernel of their own on 32x32x16 MFMAs, gemm_tn_short.hip).
 //
 // gemm_bf16_kernel: workgroup tile 256 x 256, k-block 64, 8 waves in two groups
 // of four that take turns: a k-block is four phases, each [operand reads and
@@ -471,6 +472,9 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t stream) {
       best = ns;
     }
   }
+  // Few k-blocks of TN with a write-only epilogue on 256 tiles are bound by
+  // their stores (gemm_tn_short.hip has the figures; even at about 16).
+  if (g.tn && bt == 256 && nkb <= 16 && (g.epi == kEpiBf16 || g.epi == kEpiF32)) return launch_gemm_tn_short(g, stream);
   return g.tn ? launch_epi<1>(g, bt, stream) : launch_epi<0>(g, bt, stream);
 }
 

@@ -141,6 +141,7 @@ struct GemmArgs {
   int tn;
 };
 hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t stream);
+hipError_t launch_gemm_tn_short(const GemmArgs& g, hipStream_t stream);  // a kernel that it takes
 
 // LayerNorm over rows of H (H % 8 == 0, H <= 8192), bf16 activations, fp32
 // parameters and statistics.  Forward: y, mean, rstd.  Backward: y = dx =

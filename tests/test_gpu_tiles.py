@@ -115,6 +115,26 @@ def test_gemm_tn_tiles(M, N, K):
     assert np.abs(to_np(got) - ref).max() <= 8e-3 * np.abs(ref).max()
 
 
+# TN that is written and not added, up to 16 k-blocks on 256 tiles: one row, odd and even numbers of k-blocks, a last
+# one with rows missing, and beside the limit; C's rows longer than N stay as they were past it.
+@pytest.mark.parametrize("M,N,K", [(4096, 4352, 1), (4352, 4096, 64), (4096, 4352, 65), (5120, 4096, 190), (4096, 4096, 1024),
+                                   (4096, 4096, 1025)])
+@pytest.mark.parametrize("epi", ["f32", "bf16"])
+def test_gemm_tn_short(M, N, K, epi):
+    announce(f"gemm tn short {epi} {M}x{N}x{K}")
+    g = torch.Generator().manual_seed(M + N + K)
+    a, b = (torch.randn(K, n, generator=g).to(torch.bfloat16) for n in (M, N))
+    ld = N + 8
+    c = torch.full((M, ld), 7.0, device="cuda", dtype=torch.float32 if epi == "f32" else torch.bfloat16)
+    ad, bd = a.cuda(), b.cuda()
+    L.sppo_gemm_bf16("tn", M, N, K, ad, M, bd, N, c, ld, epi)
+    torch.cuda.synchronize()
+    ref = to_np(a).T @ to_np(b)
+    got = to_np(c)
+    assert (got[:, N:] == 7.0).all()
+    assert np.abs(got[:, :N] - ref).max() <= (1e-5 if epi == "f32" else 8e-3) * np.abs(ref).max() + 1e-6
+
+
 # The split attention kernels (64 query rows, 32 or 64 keys a workgroup, four or two parts) and the wide ones beside
 # them: one row, one below, at and above a sub-block (32), a workgroup (64) and a wide tile (128), chunk boundaries off
 # all of them, GQA; the last two have enough heads for the wide kernels in some launches and the split ones in others.

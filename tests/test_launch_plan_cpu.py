@@ -73,7 +73,7 @@ def test_fp32_backward_grids_stay_launchable(plan):
 def test_gemm_tiles_fit_the_grid(plan, tn):
     """Tall products whose time estimate favours small tiles keep to a tile
     whose rows fit a grid dimension."""
-    cases = [f"gemm {tn} 0 {M} {N} {K}" for M in (65535 * 64, 65535 * 64 + 256, 6_000_128, 65535 * 128 + 256, 65535 * 256)
+    cases = [f"gemm {tn} 0 {M} {N} {K}" for M in (65532 * 64, 65536 * 64, 256 * 23438, 65538 * 128, 65535 * 256)
              for N in (256 if tn else 4, 256) for K in (64, 1664, 4096, 16384)]
     plans = plan(cases)
     for c, p in zip(cases, plans):
@@ -147,3 +147,16 @@ def test_wide_dq_of_head_size_64_by_load(plan, Hq, c0, c1, one):
 def test_forward_by_load(plan, Hq, D, c0, c1, want):
     p, = plan([f"fwd bf16 1 {Hq} {Hq} {D} {c1} {c0} {c1}"])
     assert legal(p) and want in kernels(p)[0] and f"ILi{D}E" in kernels(p)[0]
+
+
+@pytest.mark.parametrize("epi,short", [(0, True), (5, True), (4, False), (1, False)])
+def test_gemm_tn_of_few_k_blocks(plan, epi, short):
+    """Weight gradients that are written, over up to 16 k-blocks on 256 tiles;
+    those that are added, longer or smaller ones and NT keep their kernels."""
+    cases = [(1, 6144, 9984, 106), (1, 6144, 9984, 1024), (1, 6144, 9984, 1025), (1, 256, 256, 64), (0, 6144, 9984, 128)]
+    got = plan([f"gemm {tn} {epi} {M} {N} {K}" for tn, M, N, K in cases])
+    for (tn, M, N, K), p in zip(cases, got):
+        want = short and tn and M > 256 and K <= 1024
+        assert legal(p) and ("gemm_tn_short" in kernels(p)[0]) == bool(want), (M, N, K, p)
+        if want:
+            assert p[0]["grid"] == (N // 256, M // 256, 1)
