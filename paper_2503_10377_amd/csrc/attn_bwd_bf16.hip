@@ -776,7 +776,8 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_bf16_kernel(ChunkArgs a) {
 // query rows of one head times four parts of the keys (part ks has the 32-key
 // sub-blocks u = ks, ks + 4, ...), a wave each; the parts are added through LDS
 // in part order.  A sub-block's part depends on its position in the sequence
-// alone, so a row's result depends neither on the chunking nor on RG.
+// alone, so a row's result depends neither on RG nor, as long as every chunk's
+// launch takes this kernel, on the chunking.
 // bwd_dq_split is one workgroup's work: position gp of a grid nx tiles wide, in
 // the kDqSplitBytes bytes of LDS at mem.
 constexpr int kDqParts = 4;

@@ -367,8 +367,10 @@ __global__ __launch_bounds__(256, 2) void fwd_bf16_kernel(ChunkArgs a) {
 // groups of 32 query rows of one head times four parts of the keys (part ks has
 // the 32-key sub-blocks u = ks, ks + 4, ...), each wave with its own running
 // max, sum and O; the parts are added through LDS in part order.  A sub-block's
-// part depends on its position in the sequence alone, so a row's result does
-// not depend on the chunking.  Bound by the latency of a step (four sub-blocks,
+// part depends on its position in the sequence alone, so with chunk boundaries
+// on multiples of 32 rows (a wave's rows move their running maxima together) a
+// row's result does not depend on the chunking, as long as every chunk's launch
+// takes this kernel.  Bound by the latency of a step (four sub-blocks,
 // about 1.05 us against 0.42 us for each one in the kernel above); four groups
 // times two parts took the same time a step and gained nothing, one group times
 // eight parts is bound by L2 (every 32 rows stream K and V).

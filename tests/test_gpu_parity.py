@@ -116,9 +116,10 @@ def test_bf16_structured(kind):
 
 
 def test_chunked_matches_unchunked_on_gpu():
-    """Chunking is an exact rewrite: with chunk boundaries on the tile grid
-    the forward and dQ are bitwise identical to one chunk; dK/dV differ only
-    by the order of fp32 accumulation across chunks."""
+    """Chunking is an exact rewrite: with chunk boundaries on the tile grid,
+    and every launch small enough for the split kernels as here, the forward
+    and dQ are bitwise identical to one chunk; dK/dV differ only by the order
+    of fp32 accumulation across chunks."""
     B, S, Hq, Hkv, D = 1, 2048, 4, 2, 128
     res = {}
     for N in (1, 4):

@@ -1,18 +1,21 @@
 """GPU parity at the edges of the kernels' tiles and dispatch rules: sizes one
 below, at and one above a tile, remainders in every dimension, and the
 smallest sizes, against the fp64 oracle with the gates of parity.py."""
+import math
 import sys
 
 import numpy as np
 import pytest
 import torch
 
+import oracle
 from oracle import transformer_layer as T
 from paper_2503_10377_amd import sppo as L
 from paper_2503_10377_amd.chunked import ChunkedAttention
 from paper_2503_10377_amd.inputs import make_inputs
 from parity import check_all, to_np
 from test_gpu_parity import run_case
+from test_structured_gates_cpu import bf16_recipe
 
 pytestmark = pytest.mark.gpu
 
@@ -145,6 +148,67 @@ def test_gemm_tn_short(M, N, K, epi):
 def test_bf16_split_and_wide(D, B, Hq, Hkv, offsets):
     gpu, ref, off = run_case(B, offsets[-1], Hq, Hkv, D, "bf16", offsets=offsets, seed=19)
     check_all(gpu, ref, "bf16", off)
+
+
+# The wide kernels under the mask, with enough heads that no launch of a kind is split: one chunk of 1024 rows x 64 heads
+# is 512 workgroups of 128 rows (16x16x32 forward; D = 64: dQ too), two of 512 are 256 each (32x32x16; D = 64: split).
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("kind", ["sharp_self", "sharp_future", "zero_q"])
+def test_bf16_structured_wide(kind, D):
+    """The first and the last KV group against the oracle, within twice the error
+    that the bf16 rounding points alone make on these inputs (computed beside it;
+    at D = 64 sharp_self they exceed the gates derived for D = 128).  A mask off
+    by one key moves O, LSE and dV by O(1)."""
+    B, S, Hq, Hkv = 1, 1024, 64, 32
+    inp = make_inputs(B, S, Hq, Hkv, D, torch.bfloat16, seed=6, device="cuda", kind=kind)
+    qh, kh = [0, 1, 62, 63], [0, 31]
+    host = {n: to_np(t[:, :, qh if n in ("q", "do") else kh]) for n, t in inp.items()}
+    args = (host["q"], host["k"], host["v"], host["do"], 1.0 / math.sqrt(D))
+    ref, rounded = oracle.attention(*args), bf16_recipe(*args)
+    for N in (1, 2):
+        announce(f"structured wide {kind} D={D} N={N}")
+        got = walk(inp, B, S, N, Hq, Hkv, D, "bf16")
+        assert np.abs(got["lse"][:, qh] - ref["lse"]).max() <= 1e-3
+        for n in ("o", "dq", "dk", "dv"):
+            err = np.abs(got[n][:, :, qh if n in ("o", "dq") else kh] - ref[n])
+            base = np.abs(rounded[n] - ref[n])
+            assert err.max() <= 2 * base.max() + 1e-6 and err.mean() <= 2 * base.mean() + 1e-7, (n, N, err.max(), base.max())
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_bf16_ragged_wide_accumulates(D):
+    """dK/dV of the wide kernels added over chunks at boundaries off every tile
+    (the launches of the later chunks are past the split kernels' sizes)."""
+    gpu, ref, off = run_case(2, 1111, 64, 32, D, "bf16", offsets=[0, 301, 700, 1111], seed=29)
+    check_all(gpu, ref, "bf16", off)
+
+
+def test_bf16_mfma32_dq_of_head_size_64():
+    """The 32x32x16 dQ of head size 64 (17 heads, 1000 rows: 272 workgroups of 64
+    rows, three heads an XCD) at boundaries off its tiles."""
+    gpu, ref, off = run_case(1, 1333, 17, 17, 64, "bf16", offsets=[0, 1001, 1333], seed=31)
+    check_all(gpu, ref, "bf16", off)
+
+
+@pytest.mark.parametrize("Hq,S,N,same", [(32, 8192, 4, True), (4, 8192, 8, False)])
+def test_chunking_and_the_choice_of_kernels(Hq, S, N, same):
+    """Chunk boundaries on the tile grid leave O, LSE and dQ bit for bit where
+    every launch takes the same kernels (here the wide ones).  Where the chunks
+    are small enough for the split kernels and the whole is not, the keys are
+    summed in another order and against other running maxima: O and dQ differ
+    by roundings of P (or dS) and of the result to bf16, 2^-9 each on either
+    side; LSE by fp32 sums."""
+    inp = make_inputs(1, S, Hq, Hq, 128, torch.bfloat16, seed=37, device="cuda")
+    announce(f"chunking Hq={Hq} S={S} N={N}")
+    one, many = (walk(inp, 1, S, n, Hq, Hq, 128, "bf16") for n in (1, N))
+    for n in ("o", "dq"):
+        if same:
+            assert np.array_equal(one[n], many[n]), n
+        else:
+            assert np.linalg.norm(one[n] - many[n]) <= 4 * 2.0**-9 * np.linalg.norm(one[n]), n
+    assert np.abs(one["lse"] - many["lse"]).max() <= (0 if same else 2e-5)
+    for n in ("dk", "dv"):  # the order of fp32 sums, and (split) the same roundings
+        assert np.linalg.norm(one[n] - many[n]) <= (1e-5 if same else 4 * 2.0**-9) * np.linalg.norm(one[n]), n
 
 
 @pytest.mark.parametrize("Hq,Hkv,D,offsets", [(8, 2, 128, [0, 500, 1000, 1777]), (16, 16, 64, [0, 700, 1500])])
