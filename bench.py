@@ -138,10 +138,11 @@ def oracle_cpu_baseline(inp, D, sample_tokens, sample_heads):
 
 
 def kernel_source_hash(kernel):
-    """sha256 of the HIP source that defines ``kernel``."""
+    """sha256 of the HIP source that defines ``kernel`` as the workloads run
+    it (head size 128, grids of several passes)."""
     import hashlib
 
-    src = {"fwd": "attn_fwd_bf16.hip", "bwd_dkdv": "attn_bwd_bf16.hip", "bwd_dq": "attn_bwd_bf16.hip",
+    src = {"fwd": "attn_fwd_bf16.hip", "bwd_dkdv": "attn_bwd_bf16_mfma32.hip", "bwd_dq": "attn_bwd_bf16_mfma32.hip",
            "bwd_pre": "attn_bwd_bf16.hip"}[kernel]
     path = os.path.join(ROOT, "paper_2503_10377_amd", "csrc", src)
     with open(path, "rb") as f:

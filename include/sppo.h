@@ -324,7 +324,9 @@ sppo_status sppo_link_probe(sppo_ctx* ctx, size_t bytes, sppo_link_rates_t* out)
 
 /* Enable (1) or disable (0) per-kernel timing: while enabled, every kernel
  * launch is bracketed by two events on the caller's stream.  Creates the
- * events on first use. */
+ * events on first use.  The backward of a small chunk is then launched kernel
+ * by kernel too, where it otherwise does dK/dV and dQ in one launch: the same
+ * results, but the times are those of the separate launches. */
 sppo_status sppo_set_kernel_timing(sppo_ctx* ctx, int32_t enable);
 
 /* Wait for the timed kernels and return the summed durations and launch

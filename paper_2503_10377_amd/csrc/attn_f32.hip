@@ -1,6 +1,6 @@
 // fp32 forward and backward of one chunk of sequence-chunked causal
 // attention on the fp32 matrix instruction (v_mfma_f32_16x16x4_f32: fp32
-// products and fp32 accumulation), with correctly rounded expf / logf.  The
+// products and fp32 accumulation), with the device library's expf / logf.  The
 // fp32 configuration is held to 1e-4 absolute error, and its problems are
 // small, so latency and idle compute units bound it rather than the matrix
 // pipes.

@@ -20,10 +20,13 @@
 // done afterwards, one at a time.  The epilogue writes O = O^T / l (bf16)
 // and LSE = ln2 * (m + log2 l).
 //
-// Bound by power and by the softmax between the MFMAs.  16x16x32 in place of
-// 32x32x16 MFMAs, with the row max left in-lane: clock 1.65 -> 1.82 GHz, matrix
-// pipe busy 0.65 -> 0.61, 1140 -> 1180 TFLOP/s at 128K tokens x 32 heads, 1059
-// -> 1161 at 16K x GQA 32/8, D = 64 898 -> 960.
+// Bound by power (the chip holds 1.8 of its 2.4 GHz) and by the softmax between
+// the MFMAs.  With two workgroups on most compute units 16x16x32 MFMAs, the row
+// max left in-lane, take 3-6% less time than 32x32x16 ones: 32 heads, rows
+// [122880, 131072) 15.64 -> 14.97 ms, GQA 32/8, rows [12288, 16384) 840 -> 795
+// us, D = 64, 32 heads, rows [8192, 16384) 875 -> 850.  Where most units hold
+// one, attn_fwd_bf16_mfma32.hip is the faster; grids that leave units idle take
+// the split kernel further down.
 #include "sppo_kernels.h"
 #include "tile_common.h"
 

@@ -15,8 +15,9 @@
 // memory, e.g. the head dim) uses the plain map k = 32*kk + 8*g + e instead.
 //
 // At the power limit 16x16x32 is the cheaper form of a product: 256 CUs of
-// nothing but MFMAs on N(0,1) operands hold 2.03-2.06 PFLOP/s with it and
-// 1.72-1.81 with 32x32x16.
+// nothing but MFMAs hold 2.02-2.06 PFLOP/s with it and 1.72-1.86 with 32x32x16
+// on N(0,1) operands (four machines).  On constant operands, which toggle
+// little, both run at the full clock, 2.42 and 2.48.
 #pragma once
 
 #include <hip/hip_runtime.h>

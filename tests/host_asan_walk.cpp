@@ -7,7 +7,7 @@
 // repository root:
 //
 //   for f in paper_2503_10377_amd/csrc/*.hip paper_2503_10377_amd/csrc/*.cpp tests/host_asan_walk.cpp; do
-//     x=""; case $f in *attn_*_bf16.hip) x="-mllvm -amdgpu-mfma-vgpr-form";; esac
+//     x=""; case $f in *attn_*bf16*.hip|*attn_f32.hip|*gemm_bf16.hip) x="-mllvm -amdgpu-mfma-vgpr-form";; esac
 //     l=""; case $f in *.hip) l="-x hip";; esac
 //     hipcc -O1 -g -std=c++17 --offload-arch=gfx950 -Xclang -target-feature -Xclang -packed-fp32-ops \
 //       -Xarch_host -fsanitize=address -Xarch_host -fno-omit-frame-pointer \
