@@ -22,9 +22,10 @@
 // of four that take turns: a k-block is four phases, each [operand reads and
 // one half-tile DMA] then [16 MFMAs, a 64 x 32 quadrant], and the second group
 // runs half a phase behind, so on every SIMD one wave's MFMAs cover the other's
-// reads and DMA issue.  Bound by the matrix pipes at the power limit: 94% of
-// the MFMA issue rate on an otherwise idle chip (0.91 us per k-block), MFMA
-// busy 0.88 on a full one at about 1.4-1.5 GHz.  Against 8 waves in step on one
+// reads and DMA issue.  Bound by the matrix pipes at the power limit: 0.91 us
+// per k-block on an otherwise idle chip, 94% of the MFMA issue rate; on a full
+// one MFMA busy 0.64-0.76 at 1.8 GHz (counters; the epilogues are the rest, the
+// plain one 0.76).  Against 8 waves in step on one
 // barrier per k-block with 32x32x16 MFMAs (the previous kernel), TFLOP/s at
 // 8192 rows: NT 4096 x 4096 1218 -> 1431, GELU 16384 x 4096 1064 -> 1350,
 // residual 4096 x 16384 1163 -> 1426, TN 4096 x 16384 accumulate 1083 -> 1282.
